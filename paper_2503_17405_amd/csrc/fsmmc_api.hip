@@ -422,7 +422,7 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
     }
     d.tstop = (uint32_t)d.n;
 
-    if (d.kind == FSMMC_ESS && d.target == FSMMC_GP_HYPER) {  // FP64 Cholesky by a wave (n <= 128) or a block
+    if (d.kind == FSMMC_ESS && d.target == FSMMC_GP_HYPER) {  // FP64 Cholesky by a block of 1 to 8 waves
         d.Dp = d.D;
         d.N = target->n_data;
         d.pdim = target->aux;
@@ -439,7 +439,8 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         ALLOC(d.y, (size_t)d.N * 8);
         HIP_TRY_JOB(hipMemcpyAsync(d.X, target->X, (size_t)d.N * d.pdim * 8, hipMemcpyDeviceToDevice, job->stream));
         HIP_TRY_JOB(hipMemcpyAsync(d.y, target->y, (size_t)d.N * 8, hipMemcpyDeviceToDevice, job->stream));
-        HIP_TRY_JOB(gph_setup(d));
+        ALLOC(d.L, gph_dist_bytes(d.N));
+        HIP_TRY_JOB(gph_setup(d, job->stream));
         if (gph_slot_bytes(d)) ALLOC(d.gslot, gph_slot_bytes(d));
         HIP_TRY_JOB(gph_init_state(d, x0, job->stream));
         job->launches += x0 ? 2 : 1;

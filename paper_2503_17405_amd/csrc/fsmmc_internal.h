@@ -31,12 +31,12 @@ struct JobDev {
     double scales[4] = {0, 0, 0, 0};
 
     // target data (owned copies)
-    void* L = nullptr;  // Dp x Dp, zero padded (GP)
+    void* L = nullptr;  // Dp x Dp, zero padded (GP); GP_HYPER: squared distances in tiles (gph.hip)
     void* Lp = nullptr; // FP32 GP with Dp > 256: L's bf16 pieces, packed (ess_lower_pieces_halfwords)
     void* y = nullptr;  // Dp (GP) or Np (LOGREG) labels / observations
     void* X = nullptr;  // LOGREG: Np x Dp, zero padded
     void* Xb = nullptr; // LOGREG: X as three bf16 pieces, row- and d-major per 32-row chunk (logreg.hip)
-    void* gslot = nullptr;  // GP_HYPER with n > 128: a Cholesky work matrix per persistent block
+    void* gslot = nullptr;  // GP_HYPER with n >= 256: finished Cholesky tiles, per persistent block
     void* prec = nullptr;
 
     // common chain state
@@ -134,8 +134,9 @@ hipError_t mog_eval(const JobDev& j, int n, const float* pts, float* G, float* U
 // draw, 2 vmap padding of that draw
 int gph_max_obs();
 size_t gph_slot_bytes(const JobDev& j);  // after gph_setup
+size_t gph_dist_bytes(int N);            // squared distances of the inputs (j.L)
 int gph_max_inputs();
-hipError_t gph_setup(JobDev& j);
+hipError_t gph_setup(JobDev& j, hipStream_t s);
 hipError_t gph_init_state(const JobDev& j, const void* x0, hipStream_t s);
 hipError_t gph_run(const JobDev& j, int mode, uint32_t draw, unsigned long long* ticket, hipStream_t s);
 

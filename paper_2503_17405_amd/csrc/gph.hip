@@ -6,32 +6,14 @@
 // an O(n^3) Cholesky factorisation inside every loop iteration: the regime
 // where the log-density dominates each transition and the FSM gain tracks R(m).
 //
-// Persistent kernel, one wavefront per block and per chain at a time: the
-// wave takes chains from a device ticket counter and runs each one's ESS FSM
-// (INIT, SHRINK, DONE; every step = one proposal and one likelihood) to its
-// draw budget, so no chain waits for another.  The likelihood is computed by
-// the wave in FP64 (kernel matrices of smooth kernels are badly
-// conditioned; the 3-D chain state is FP64 too):
-//   * C's lower triangle is built in LDS (packed rows, n(n+1)/2 doubles) from
-//     the inputs staged in LDS;
-//   * right-looking Cholesky, column by column: the column below the
-//     diagonal is scaled (lane i mod 64 holds rows i) into registers and an
-//     LDS column buffer, the forward solve L z = y runs alongside (y in
-//     registers), and each lane applies the rank-1 update to its own rows of
-//     the trailing triangle, four columns at a time; a block barrier (one
-//     wave) orders the LDS updates;
-//   * log L = -|z|^2 / 2 - sum_j log L_jj; -inf when a pivot is not positive.
-// More than 96 observations (the paper's data set has 414): one block of
-// four waves per chain (gph_big_kernel), C in a global slot of the block
-// (n rounded up to 32, identity padding), blocked right-looking Cholesky
-// with 32-column panels:
-//   * wave 0 factors the panel's diagonal block in LDS (lane per row) and
-//     solves its part of L z = y;
-//   * the rows below are solved against it (thread per row, right-looking
-//     inside the row) into an LDS copy of the panel, and their y entries
-//     take the panel's part of the forward solve;
-//   * each wave updates 32 x 32 tiles of the trailing triangle in the slot,
-//     a 4 x 4 block per lane, with the panel's columns read from LDS.
+// Persistent kernel: a block of NW waves takes chains from a device ticket
+// counter and runs each one's ESS FSM (INIT, SHRINK, DONE; every step = one
+// proposal and one likelihood) to its draw budget, so no chain waits for
+// another.  The likelihood is computed by the block in FP64 (kernel matrices
+// of smooth kernels are badly conditioned; the 3-D chain state is FP64 too) on
+// the matrix cores, from 16 x 16 tiles held in registers (gph_loglik below).
+// The squared distances |x_i - x_k|^2 do not depend on theta: they are formed
+// once per job (gph_dist_kernel), laid out tile by tile as the lanes read them.
 // The library builds with contraction off, so the updates are written as
 // explicit FMAs (one instruction and one rounding per term).
 // The synchronized runtime launches the kernel once per draw (tstop =
@@ -42,18 +24,17 @@
 
 namespace fsmmc {
 
-constexpr int kGphMaxN = 96;      // observations, in-wave likelihood: up to two rows per lane
-constexpr int kGphBigMaxN = 512;  // observations, block likelihood (LDS holds a 32-column panel)
-constexpr int kGphBigWaves = 4;   // waves per block of the block likelihood
-constexpr int kGphMaxP = 16;      // input dimension
+constexpr int kGphMaxN = 512;  // observations
+constexpr int kGphMaxP = 16;   // input dimension
+constexpr int kGphTile = 256;  // doubles of a 16 x 16 tile
 
 struct GphK {
     int m, n, N, p;
     uint32_t tstop;
     uint64_t seed;
     double jitter;
-    const double* X;  // N x p inputs
-    const double* y;  // N outputs
+    const double* y;   // N outputs
+    const double* r2;  // squared distances, tile (I, J <= I) at I (I + 1) / 2 + J (gph_dist_kernel)
     double *th, *nu;  // [chain][3]
     double *lx, *phi, *pmin, *pmax, *logu;
     int32_t *k, *evals;
@@ -64,17 +45,9 @@ struct GphK {
     unsigned long long* ctr;
     int32_t* maxN;
     double* sink;
-    double* slots;  // block likelihood: ld x ld doubles per block
-    int ld;         // N rounded up to 32
+    double* slots;  // N >= 256: finished tiles of the leading columns, slot_tiles per block
+    int slot_tiles;
 };
-
-__device__ __forceinline__ int gph_next_chain(unsigned long long* q, unsigned long long base, int m, int lane)
-{
-    unsigned long long tk = 0;
-    if (lane == 0) tk = atomicAdd(q, 1ull);
-    const unsigned long long off = (unsigned long long)uni((int64_t)tk) - base;
-    return off < (unsigned long long)m ? (int)off : m;
-}
 
 __device__ __forceinline__ double rl(double v, int l)
 {
@@ -84,405 +57,456 @@ __device__ __forceinline__ double rl(double v, int l)
     return __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
 }
 
-// log L(th) by the wave; A: n(n+1)/2 doubles of LDS (packed rows), cb: n
-// doubles of LDS (the current column), Xs: the inputs in LDS.  Lane l owns
-// rows l and l + 64.  Column j: the lanes scale their entries of column j
-// (registers and cb), then every lane updates its own rows' entries k of the
-// trailing triangle, four consecutive k at a time with L_kj read from cb (one
-// broadcast per k): n^2 / 8 independent iteration groups instead of a
-// latency-bound sweep.
-__device__ double gph_loglik(const GphK& a, const double* th, double* A, double* cb, const double* Xs, int lane)
+// ------------------------------------------------------------ likelihood
+// log L(th) by a block of NW waves.  The matrix is C with y as one more row (row
+// n), so that the factorisation's row n is the forward solve z = L^-1 y; it is
+// cut into 16 x 16 tiles, T tile columns and R tile rows (R = T, or T + 1 when
+// 16 divides n).
+//
+// Tile layout ("fragments"): lane (q, i) = (lane / 16, lane % 16) holds row i,
+// columns q, q + 4, q + 8, q + 12.  For v_mfma_f64_16x16x4_f64 this is the
+// operand layout of A and of B^T (k step s: column 4 s + q) and, with the
+// product taken transposed, the layout of the result: a finished tile is the
+// next product's operand with no data movement.  Registers hold minus the
+// remaining matrix, so every update is a plain accumulation.
+//
+// Right-looking over the tile columns t.  The wave that owns row t factors the
+// diagonal tile (gph_factor) and publishes minus its inverse in LDS; every wave
+// then takes its rows' tiles of column t to L_It = A_It L_tt^-T (four MFMAs),
+// publishes them in LDS and updates its remaining tiles with L_It L_ct^T (four
+// MFMAs each, L_ct from LDS).  Two barriers per tile column.  Wave w owns rows
+// w and 2 NW - 1 - w: 2 NW + 1 tiles whatever w, all in registers (position p:
+// column p of the first row for p <= w, column 2 NW - p of the second above).
+//
+// LEAD (n >= 256, more than 16 tile rows): the leading R - 16 tile columns go
+// first, in panels of four columns (rows dealt to the waves in turn, up to four
+// each); their finished tiles go to the block's slot in memory, and the
+// panels after them and the trailing 16 rows start from C minus the products
+// of those tiles.
+//
+// What bounds it: the FP64 matrix and vector units have the same rate (one
+// MFMA = 64 cycles of its SIMD = 16 FMAs), but an FMA form needs its operands
+// broadcast through LDS (four times the LDS bytes per flop) or by lane reads;
+// what is left is the serial chain of the diagonal tiles (about 3000 cycles
+// each).
+// @MEASURED@
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// A tile in memory: doubles [half][lane][2], so a lane's four values are two
+// 16-byte accesses that fill whole lines.
+__device__ __forceinline__ d4 tile_load(const double* t, int lane)
 {
-    const int n = a.N, p = a.p;
+    const double2 u = reinterpret_cast<const double2*>(t)[lane];
+    const double2 v = reinterpret_cast<const double2*>(t)[64 + lane];
+    return d4{u.x, u.y, v.x, v.y};
+}
+
+__device__ __forceinline__ void tile_store(double* t, int lane, const d4& v)
+{
+    reinterpret_cast<double2*>(t)[lane] = make_double2(v[0], v[1]);
+    reinterpret_cast<double2*>(t)[64 + lane] = make_double2(v[2], v[3]);
+}
+
+// acc + (a b^T)^T, a and b tiles as fragments
+__device__ __forceinline__ d4 tile_mac(const d4& a, const d4& b, d4 acc)
+{
+#pragma unroll
+    for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+    return acc;
+}
+
+// What a wave gathers along the way: pivots as mantissa product and exponent
+// sum (lanes 0-15), |z|^2 (the lanes of row n), a pivot that was not positive.
+struct GphSum {
+    double pm = 1.0, zz = 0.0;
+    int pe = 0, bad = 0;
+};
+
+// The diagonal tile: acc = minus the remaining tile.  Lanes 0-15 take the
+// tile's rows whole, lanes 16-31 the identity's: eliminating its first nc
+// columns leaves L in the former and L^-T in the latter, and minus L^-1 goes to
+// inv as a tile.  yrow: the tile's row that is row n of the matrix, or -1.
+__device__ __forceinline__ void gph_factor(const d4& acc, int nc, int yrow, int lane, double* inv, GphSum& G)
+{
+    const int i = lane & 15;
+    const bool unit = (lane & 16) != 0;
+    double W[16];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        double a, b, c[4];
+        lane_pair<16>(-acc[r], a, b);  // a: rows 0 and 2 of 16 lanes, b: rows 1 and 3
+        lane_pair<32>(a, c[0], c[2]);
+        lane_pair<32>(b, c[1], c[3]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) W[4 * r + q] = unit ? (4 * r + q == i ? 1.0 : 0.0) : c[q];
+    }
+    double piv = 1.0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        if (j < nc) {
+            const double ajj = rl(W[j], j);
+            G.bad |= !(ajj > 0.0);
+            // 1 / sqrt(ajj): the hardware estimate (about 2^-26) and one
+            // third-order step, y + y e (1/2 + 3/8 e), e = 1 - a y^2
+            const double y0 = __builtin_amdgcn_rsq(ajj);
+            const double e = fma(-(ajj * y0), y0, 1.0);
+            const double r = fma(y0 * e, fma(0.375, e, 0.5), y0);
+            if (lane == j) piv = ajj;
+            W[j] *= r;
+#pragma unroll
+            for (int u = j + 1; u < 16; ++u) W[u] = fma(-W[j], rl(W[j], u), W[u]);
+            __builtin_amdgcn_sched_barrier(0);  // one column's lane reads in scalar registers at a time
+        }
+    }
+    G.pm *= __builtin_amdgcn_frexp_mant(piv);
+    G.pe += __builtin_amdgcn_frexp_exp(piv);
+    if (lane == yrow) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+            if (j < nc) G.zz = fma(W[j], W[j], G.zz);
+    }
+    if (unit && lane < 32) {  // lane 16 + i: column i of L^-1, element u at (row u, column i)
+#pragma unroll
+        for (int u = 0; u < 16; ++u) inv[((i >> 3) * 64 + (i & 3) * 16 + u) * 2 + ((i >> 2) & 1)] = -W[u];
+    }
+}
+
+// Minus tile (I, J) of C (with y as row n).
+__device__ __forceinline__ d4 gph_tile_of_c(const GphK& a, double tau2, double lam2, double s2, int I, int J, int lane)
+{
+    const int row = 16 * I + (lane & 15), col0 = 16 * J + (lane >> 4);
+    const d4 r2 = tile_load(a.r2 + (size_t)(I * (I + 1) / 2 + J) * kGphTile, lane);
+    d4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = -(tau2 * exp(-lam2 * r2[r]) + (row == col0 + 4 * r ? s2 : 0.0));
+    if (16 * I + 16 > a.N) {  // the tile row that holds row n and the padding below it
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int col = col0 + 4 * r;
+            if (row >= a.N) v[r] = row == a.N && col < a.N ? -a.y[col] : 0.0;
+        }
+    }
+    return v;
+}
+
+// LDS doubles: the published column (2 NW tiles), the inverse, three sums per wave
+template <int NW>
+constexpr int gph_lds_doubles() { return (2 * NW + 1) * kGphTile + 3 * NW; }
+
+template <int NW, bool LEAD>
+__device__ double gph_loglik(const GphK& a, const double* th, double* slot, double* sm)
+{
+    constexpr int RW = 2 * NW;
+    const int n = a.N, T = (n + 15) >> 4, R = (n + 16) >> 4, yrow = n & 15;
+    const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
+    double* colb = sm;
+    double* inv = sm + RW * kGphTile;
+    double* red = inv + kGphTile;
     const double tau2 = th[0] * th[0], lam2 = th[1] * th[1], s2 = th[2] * th[2] + a.jitter;
-    for (int i = 0; i < n; ++i) {
-        const int base = i * (i + 1) / 2;
-        for (int k = lane; k <= i; k += 64) {
-            double r2 = 0.0;
-            for (int d = 0; d < p; ++d) {
-                const double e = Xs[i * p + d] - Xs[k * p + d];
-                r2 = fma(e, e, r2);
+    GphSum G;
+    // L_It from minus the remaining tile x; its part of |z|^2 if it holds row n
+    auto solve = [&](const d4& iv, const d4& x, int I) {
+        const d4 L = tile_mac(iv, x, d4{0.0, 0.0, 0.0, 0.0});
+        if (I == R - 1 && (lane & 15) == yrow) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) G.zz = fma(L[r], L[r], G.zz);
+        }
+        return L;
+    };
+    const int base = LEAD ? R - RW : 0;  // rows and columns below go first
+    if constexpr (LEAD) {
+        auto at = [&](int I, int k) { return slot + (size_t)(k * R + I) * kGphTile; };
+        for (int P = 0; P < base; P += 4) {
+            const int pc = min(4, base - P);
+            d4 acc[4][4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int rel = wave + NW * s, I = P + rel;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    acc[s][c] = I < R && c < pc && c <= rel ? gph_tile_of_c(a, tau2, lam2, s2, I, P + c, lane)
+                                                            : d4{0.0, 0.0, 0.0, 0.0};
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
-            A[base + k] = tau2 * exp(-lam2 * r2) + (i == k ? s2 : 0.0);
-        }
-    }
-    double yv[2];
-    int rb[2];
+            for (int k = 0; k < P; ++k) {
+                d4 A[4];
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int i = lane + 64 * r;
-        yv[r] = i < n ? a.y[i] : 0.0;
-        rb[r] = i * (i + 1) / 2;
-    }
-    __syncthreads();
-    double quad = 0.0, ld = 0.0;
-    for (int j = 0; j < n; ++j) {
-        const double ajj = A[j * (j + 1) / 2 + j];
-        if (!(ajj > 0.0)) return -INFINITY;  // wave-uniform
-        const double ljj = sqrt(ajj);
-        ld += log(ljj);
-        // column j below the diagonal: registers and cb
-        double col[2];
+                for (int c = 0; c < 4; ++c) A[c] = tile_load(at(P + min(c, pc - 1), k), lane);
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int i = lane + 64 * r;
-            const bool own = i > j && i < n;
-            col[r] = own ? A[rb[r] + j] / ljj : 0.0;
-            if (own) cb[i] = col[r];
-        }
-        // forward solve alongside: z_j = y_j / L_jj, y_i -= L_ij z_j
-        const double zj = (j < 64 ? rl(yv[0], j) : rl(yv[1], j - 64)) / ljj;
-        quad += zj * zj;
+                for (int s = 0; s < 4; ++s) {
+                    const int I = P + wave + NW * s;
+                    if (I >= R) continue;
+                    const d4 B = tile_load(at(I, k), lane);
 #pragma unroll
-        for (int r = 0; r < 2; ++r) yv[r] = fma(-col[r], zj, yv[r]);
-        __syncthreads();  // cb complete
-        // trailing triangle: A_ik -= L_ij L_kj for j < k <= i, k in groups of four
-        for (int k0 = j + 1; k0 < n; k0 += 4) {
-            double lk[4];
+                    for (int c = 0; c < 4; ++c) acc[s][c] = tile_mac(A[c], B, acc[s][c]);
+                }
+            }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) lk[q] = k0 + q < n ? cb[k0 + q] : 0.0;
+            for (int t = 0; t < 4; ++t) {
+                if (t >= pc) break;
+                if (wave == t) gph_factor(acc[0][t], 16, -1, lane, inv, G);
+                __syncthreads();
+                const d4 iv = tile_load(inv, lane);
+                d4 L[4];
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const int i = lane + 64 * r;
-                if (i >= k0 && i < n) {
-                    double* ar = A + rb[r] + k0;
-                    double v[4];
+                for (int s = 0; s < 4; ++s) {
+                    const int rel = wave + NW * s, I = P + rel;
+                    if (rel > t && I < R) {
+                        L[s] = solve(iv, acc[s][t], I);
+                        tile_store(at(I, P + t), lane, L[s]);
+                        if (rel < pc) tile_store(colb + rel * kGphTile, lane, L[s]);
+                    }
+                }
+                __syncthreads();
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = k0 + q <= i ? ar[q] : 0.0;
+                for (int u = t + 1; u < 4; ++u) {
+                    if (u >= pc) break;
+                    const d4 A = tile_load(colb + u * kGphTile, lane);
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        if (k0 + q <= i) ar[q] = fma(-col[r], lk[q], v[q]);
+                    for (int s = 0; s < 4; ++s)
+                        if (wave + NW * s >= u && P + wave + NW * s < R) acc[s][u] = tile_mac(A, L[s], acc[s][u]);
                 }
             }
         }
-        __syncthreads();  // the trailing triangle is updated; cb may be rewritten
     }
-    return -0.5 * quad - ld;
+    // the trailing rows base .. R - 1, all tiles in registers
+    const int ra = wave, rb = RW - 1 - wave;  // this wave's rows, relative to base
+    const bool hasa = base + ra < R, hasb = base + rb < R;
+    d4 acc[RW + 1];
+#pragma unroll
+    for (int p = 0; p <= RW; ++p) {
+        const bool second = p > wave;
+        const int I = base + (second ? rb : ra), J = base + (second ? RW - p : p);
+        acc[p] = I < R && J < T ? gph_tile_of_c(a, tau2, lam2, s2, I, J, lane) : d4{0.0, 0.0, 0.0, 0.0};
+        __builtin_amdgcn_sched_barrier(0);  // one tile's exponentials at a time (registers)
+    }
+    if constexpr (LEAD) {
+        // minus the leading columns' products: column k of the finished tiles
+        // through LDS, the next one's loads in flight
+        constexpr int NV = RW * kGphTile / 2 / (64 * NW);  // 16-byte units per thread
+        double2 nx[NV];
+        auto fetch = [&](int k) {
+            const double2* src = reinterpret_cast<const double2*>(slot + (size_t)(k * R + base) * kGphTile);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) nx[v] = src[v * 64 * NW + threadIdx.x];
+        };
+        fetch(0);
+        for (int k = 0; k < base; ++k) {
+            __syncthreads();  // the previous column has been read
+#pragma unroll
+            for (int v = 0; v < NV; ++v) reinterpret_cast<double2*>(colb)[v * 64 * NW + threadIdx.x] = nx[v];
+            __syncthreads();
+            if (k + 1 < base) fetch(k + 1);
+            const d4 La = tile_load(colb + ra * kGphTile, lane), Lb = tile_load(colb + rb * kGphTile, lane);
+#pragma unroll
+            for (int p = 0; p <= RW; ++p) {
+                const bool second = p > wave;
+                const d4 A = tile_load(colb + (second ? RW - p : p) * kGphTile, lane);
+                if (second)
+                    acc[p] = tile_mac(A, Lb, acc[p]);
+                else
+                    acc[p] = tile_mac(A, La, acc[p]);
+            }
+        }
+        __syncthreads();
+    }
+    const int nt = T - base;
+    for (int t = 0; t < nt; ++t) {
+        if (wave == (t < NW ? t : RW - 1 - t)) {  // the owner of row t: its diagonal tile is at position w or w + 1
+            d4 d = acc[0];
+            const int pd = t < NW ? wave : wave + 1;
+#pragma unroll
+            for (int p = 1; p <= RW; ++p)
+                if (p == pd) d = acc[p];
+            const bool last = base + t == R - 1;
+            gph_factor(d, min(16, n - 16 * (base + t)), last ? yrow : -1, lane, inv, G);
+        }
+        __syncthreads();
+        const d4 iv = tile_load(inv, lane);
+        d4 La = d4{0.0, 0.0, 0.0, 0.0}, Lb = La;
+        if (ra > t && hasa) {
+            d4 x = acc[0];
+#pragma unroll
+            for (int p = 1; p < NW; ++p)
+                if (p == t) x = acc[p];
+            La = solve(iv, x, base + ra);
+            tile_store(colb + ra * kGphTile, lane, La);
+        }
+        if (rb > t && hasb) {
+            d4 x = acc[RW];
+#pragma unroll
+            for (int p = 1; p < RW; ++p)
+                if (p == t) x = acc[RW - p];
+            Lb = solve(iv, x, base + rb);
+            tile_store(colb + rb * kGphTile, lane, Lb);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p <= RW; ++p) {
+            const bool second = p > wave;
+            const int c = second ? RW - p : p;
+            if (c <= t || base + c >= T || !(second ? hasb : hasa)) continue;
+            const d4 A = tile_load(colb + c * kGphTile, lane);
+            if (second)
+                acc[p] = tile_mac(A, Lb, acc[p]);
+            else
+                acc[p] = tile_mac(A, La, acc[p]);
+        }
+    }
+    // sums over the lanes, then over the waves in order
+    const double lg = wave_sum(log(G.pm) + (double)G.pe * 0.69314718055994530942);
+    const double zz = wave_sum(G.zz);
+    const int bad = __any(G.bad) ? 1 : 0;
+    if constexpr (NW == 1) return bad ? -INFINITY : -0.5 * zz - 0.5 * lg;
+    if (lane == 0) {
+        red[3 * wave] = lg;
+        red[3 * wave + 1] = zz;
+        red[3 * wave + 2] = bad ? 1.0 : 0.0;
+    }
+    __syncthreads();
+    double slg = 0.0, szz = 0.0, sbad = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        slg += red[3 * w];
+        szz += red[3 * w + 1];
+        sbad += red[3 * w + 2];
+    }
+    return sbad != 0.0 ? -INFINITY : -0.5 * szz - 0.5 * slg;
 }
 
-// One FSM step of chain c (ESS: INIT or SHRINK, then the proposal and its
-// likelihood, accept -> DONE).  Returns 1 when the step ended a draw.
+// Squared distances of the inputs, one thread per element of a tile; rows and
+// columns past N hold 0 (gph_tile_of_c replaces them or nothing reads them).
+__global__ __launch_bounds__(256) void gph_dist_kernel(const double* X, int N, int p, double* r2)
+{
+    int I = (int)((sqrt(8.0 * blockIdx.x + 1.0) - 1.0) * 0.5);
+    while ((I + 1) * (I + 2) / 2 <= (int)blockIdx.x) ++I;
+    while (I * (I + 1) / 2 > (int)blockIdx.x) --I;
+    const int J = (int)blockIdx.x - I * (I + 1) / 2;
+    const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
+    const int i = 16 * I + (lane & 15), k = 16 * J + (lane >> 4) + 4 * r;
+    double s = 0.0;
+    if (i < N && k < N)
+        for (int d = 0; d < p; ++d) {
+            const double e = X[i * p + d] - X[k * p + d];
+            s = fma(e, e, s);
+        }
+    r2[(size_t)blockIdx.x * kGphTile + ((r >> 1) * 64 + lane) * 2 + (r & 1)] = s;
+}
+
+// A chain's state while the block steps it, in LDS: the likelihood needs every
+// register, and only wave 0 runs the FSM's own arithmetic.
 struct GphState {
     double th[3], nu[3], lx, phi, pmin, pmax, logu;
-    int k, evals;
+    double tp[3];  // the proposal of the step in progress
+    int64_t budget;
+    int k, evals, go;
     uint32_t t;
 };
 
-template <typename LL>
-__device__ __forceinline__ int gph_step(const GphK& a, int c, GphState& S, LL loglik, int lane, uint32_t* guard)
+// First half of an FSM step of chain c (ESS: INIT or SHRINK, then the proposal
+// into tp); wave 0, lane 0 writes.
+__device__ __forceinline__ void gph_propose(const GphK& a, int c, GphState& S, int lane)
 {
-    if (S.k == 1) {  // INIT: direction, threshold, first angle and bracket
+    double nu[3], phi, pmin, pmax, logu = S.logu;
+    int evals;
+    if (uni(S.k) == 1) {  // INIT: direction, threshold, first angle and bracket
 #pragma unroll
-        for (int d = 0; d < 3; ++d) S.nu[d] = normal_at<double>(a.seed, (uint32_t)c, S.t, ROLE_NU, 0, (uint32_t)d);
-        S.logu = log(uniform<double>(a.seed, (uint32_t)c, S.t, ROLE_THRESH, 0));
-        S.phi = 2.0 * 3.14159265358979323846 * uniform<double>(a.seed, (uint32_t)c, S.t, ROLE_ANGLE, 0);
-        S.pmin = S.phi - 2.0 * 3.14159265358979323846;
-        S.pmax = S.phi;
-        S.evals = 0;
+        for (int d = 0; d < 3; ++d) nu[d] = normal_at<double>(a.seed, (uint32_t)c, S.t, ROLE_NU, 0, (uint32_t)d);
+        logu = log(uniform<double>(a.seed, (uint32_t)c, S.t, ROLE_THRESH, 0));
+        phi = 2.0 * 3.14159265358979323846 * uniform<double>(a.seed, (uint32_t)c, S.t, ROLE_ANGLE, 0);
+        pmin = phi - 2.0 * 3.14159265358979323846;
+        pmax = phi;
+        evals = 0;
     } else {  // SHRINK: the bracket moves to the rejected angle, draw again
-        if (S.phi < 0.0)
-            S.pmin = S.phi;
-        else
-            S.pmax = S.phi;
-        S.phi = S.pmin + (S.pmax - S.pmin) * uniform<double>(a.seed, (uint32_t)c, S.t, ROLE_ANGLE, (uint32_t)S.evals);
-    }
-    const double cs = cos(S.phi), sn = sin(S.phi);
-    double tp[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) tp[d] = S.th[d] * cs + S.nu[d] * sn;
-    const double lp = loglik(tp);
-    S.evals += 1;
+        for (int d = 0; d < 3; ++d) nu[d] = S.nu[d];
+        phi = S.phi;
+        pmin = phi < 0.0 ? phi : S.pmin;
+        pmax = phi < 0.0 ? S.pmax : phi;
+        evals = S.evals;
+        phi = pmin + (pmax - pmin) * uniform<double>(a.seed, (uint32_t)c, S.t, ROLE_ANGLE, (uint32_t)evals);
+    }
+    const double cs = cos(phi), sn = sin(phi);
+    if (lane == 0) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            S.nu[d] = nu[d];
+            S.tp[d] = S.th[d] * cs + nu[d] * sn;
+        }
+        S.phi = phi;
+        S.pmin = pmin;
+        S.pmax = pmax;
+        S.logu = logu;
+        S.evals = evals;
+    }
+}
+
+// Second half: accept (DONE: emit, then INIT of the next draw) or SHRINK next;
+// one lane.  lp = log L(tp).
+__device__ __forceinline__ void gph_decide(const GphK& a, int c, GphState& S, double lp, uint32_t* guard)
+{
+    const int evals = S.evals + 1;
     const bool acc = lp - S.lx > S.logu;
-    const bool stop = !acc && S.evals >= kEssMaxEvals;
-    if (!acc && !stop) {
+    S.evals = evals;
+    S.budget -= 1;
+    if (!acc && evals < kEssMaxEvals) {
         S.k = 2;
-        return 0;
+        return;
     }
     if (acc) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) S.th[d] = tp[d];
+        for (int d = 0; d < 3; ++d) S.th[d] = S.tp[d];
         S.lx = lp;
     } else {
         *guard += 1;
     }
-    // DONE: emit, then INIT of the next draw
-    if (lane < 3) a.out[((size_t)c * a.n + S.t) * 3 + lane] = lane == 0 ? S.th[0] : (lane == 1 ? S.th[1] : S.th[2]);
-    if (lane == 0) a.counts[(size_t)c * a.n + S.t] = S.evals;
-    S.t += 1;
+    const uint32_t t = S.t;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) a.out[((size_t)c * a.n + t) * 3 + d] = S.th[d];
+    a.counts[(size_t)c * a.n + t] = evals;
+    S.t = t + 1;
     S.k = 1;
-    return 1;
 }
 
+// One lane.
 __device__ __forceinline__ void gph_load(const GphK& a, int c, GphState& S)
 {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        S.th[d] = uni(a.th[(size_t)c * 3 + d]);
-        S.nu[d] = uni(a.nu[(size_t)c * 3 + d]);
+        S.th[d] = a.th[(size_t)c * 3 + d];
+        S.nu[d] = a.nu[(size_t)c * 3 + d];
     }
-    S.lx = uni(a.lx[c]);
-    S.phi = uni(a.phi[c]);
-    S.pmin = uni(a.pmin[c]);
-    S.pmax = uni(a.pmax[c]);
-    S.logu = uni(a.logu[c]);
-    S.k = uni(a.k[c]);
-    S.evals = uni(a.evals[c]);
-    S.t = uni(a.t[c]);
+    S.lx = a.lx[c];
+    S.phi = a.phi[c];
+    S.pmin = a.pmin[c];
+    S.pmax = a.pmax[c];
+    S.logu = a.logu[c];
+    S.budget = a.budget[c];
+    S.k = a.k[c];
+    S.evals = a.evals[c];
+    S.t = a.t[c];
 }
 
-__device__ __forceinline__ void gph_store(const GphK& a, int c, const GphState& S, int lane)
+__device__ __forceinline__ void gph_store(const GphK& a, int c, const GphState& S)
 {
-    if (lane == 0) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            a.th[(size_t)c * 3 + d] = S.th[d];
-            a.nu[(size_t)c * 3 + d] = S.nu[d];
-        }
-        a.lx[c] = S.lx;
-        a.phi[c] = S.phi;
-        a.pmin[c] = S.pmin;
-        a.pmax[c] = S.pmax;
-        a.logu[c] = S.logu;
-        a.k[c] = S.k;
-        a.evals[c] = S.evals;
-        a.t[c] = S.t;
+    for (int d = 0; d < 3; ++d) {
+        a.th[(size_t)c * 3 + d] = S.th[d];
+        a.nu[(size_t)c * 3 + d] = S.nu[d];
     }
+    a.lx[c] = S.lx;
+    a.phi[c] = S.phi;
+    a.pmin[c] = S.pmin;
+    a.pmax[c] = S.pmax;
+    a.logu[c] = S.logu;
+    a.budget[c] = S.budget;
+    a.k[c] = S.k;
+    a.evals[c] = S.evals;
+    a.t[c] = S.t;
 }
 
-__device__ __forceinline__ void gph_stage(const GphK& a, double* Xs)
-{
-    for (int i = threadIdx.x; i < a.N * a.p; i += blockDim.x) Xs[i] = a.X[i];
-    __syncthreads();
-}
-
-// mode 0: FSM (to tstop or through the budget); mode 1: one draw of the
-// synchronized runtime (tstop = draw + 1), recording its largest count;
-// mode 2: vmap padding of draw `draw`.
-__global__ __launch_bounds__(64) void gph_kernel(GphK a, unsigned long long* q, unsigned long long base, int mode,
-                                                 uint32_t draw)
-{
-    extern __shared__ double gsm[];
-    double* Xs = gsm;
-    double* A = gsm + ((a.N * a.p + 1) & ~1);
-    double* cb = A + a.N * (a.N + 1) / 2;
-    gph_stage(a, Xs);
-    const int lane = threadIdx.x;
-    unsigned long long steps = 0, padded = 0;
-    uint32_t guard = 0;
-    for (;;) {
-        const int c = gph_next_chain(q, base, a.m, lane);
-        if (c >= a.m) break;
-        if (mode == 2) {
-            const int reps = a.maxN[draw] - uni(a.counts[(size_t)c * a.n + draw]);
-            double th[3], acc = 0.0;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) th[d] = uni(a.th[(size_t)c * 3 + d]);
-            for (int r = 0; r < reps; ++r) acc += gph_loglik(a, th, A, cb, Xs, lane);
-            if (reps > 0 && lane == 0) a.sink[c] = acc;
-            padded += (unsigned long long)max(reps, 0);
-            continue;
-        }
-        GphState S;
-        gph_load(a, c, S);
-        const uint32_t stop = mode == 1 ? draw + 1 : a.tstop;
-        if (S.t >= stop) continue;
-        const uint32_t t0 = S.t;
-        int64_t budget = uni((int64_t)a.budget[c]);
-        while (S.t < stop && budget > 0) {
-            (void)gph_step(a, c, S, [&](const double* tp) { return gph_loglik(a, tp, A, cb, Xs, lane); }, lane,
-                           &guard);
-            ++steps;
-            --budget;
-        }
-        gph_store(a, c, S, lane);
-        if (lane == 0) a.budget[c] = budget;
-        if (mode == 1 && lane == 0 && S.t > t0) atomicMax(&a.maxN[t0], a.counts[(size_t)c * a.n + t0]);
-    }
-    if (lane == 0) {
-        if (steps) atomicAdd(&a.ctr[0], steps);
-        if (padded) atomicAdd(&a.ctr[1], padded);
-        if (guard) atomicAdd(&a.ctr[2], (unsigned long long)guard);
-    }
-}
-
-// Starting state: theta (from x0 or a prior draw N(0, I) on the INIT stream)
-// and its log-likelihood, one wave per chain.
-__global__ __launch_bounds__(64) void gph_init_kernel(GphK a, int has_x0)
-{
-    extern __shared__ double gsm[];
-    double* Xs = gsm;
-    double* A = gsm + ((a.N * a.p + 1) & ~1);
-    double* cb = A + a.N * (a.N + 1) / 2;
-    gph_stage(a, Xs);
-    const int lane = threadIdx.x;
-    for (int c = blockIdx.x; c < a.m; c += gridDim.x) {
-        double th[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-            th[d] = has_x0 ? uni(a.th[(size_t)c * 3 + d]) : normal_at<double>(a.seed, (uint32_t)c, 0, ROLE_INIT, 0, (uint32_t)d);
-        const double lx = gph_loglik(a, th, A, cb, Xs, lane);
-        if (lane == 0) {
-#pragma unroll
-            for (int d = 0; d < 3; ++d) a.th[(size_t)c * 3 + d] = th[d];
-            a.lx[c] = lx;
-            a.k[c] = 1;
-        }
-    }
-}
-
-// ------------------------------------------------------------ n > 96
-// LDS of the block likelihood, in doubles: the panel below the diagonal block
-// [32][ld - 32] (column t, row r), the diagonal block [32][33], the
-// reciprocal pivots [32], y [ld], and 8 scalars.
-__host__ __device__ constexpr size_t gph_big_lds_doubles(int ld) { return 32 * (size_t)(ld - 32) + 32 * 33 + 32 + ld + 8; }
-
-// log L(th) by the block (kGphBigWaves waves) with C in `slot` (ld x ld, row-major,
-// lower triangle).  The result is the same in every thread.
-__device__ double gph_loglik_big(const GphK& a, const double* th, double* slot, double* sm)
-{
-    const int ld = a.ld, n = a.N, p = a.p;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int pr = ld - 32;  // panel row pitch
-    double* Lp = sm;
-    double* Ds = Lp + 32 * (size_t)pr;
-    double* rinv = Ds + 32 * 33;
-    double* yv = rinv + 32;
-    double* red = yv + ld;  // [0] sum log L_jj, [1] |z|^2, [2] a pivot was not positive
-    const double tau2 = th[0] * th[0], lam2 = th[1] * th[1], s2 = th[2] * th[2] + a.jitter;
-    // C's lower triangle; rows and columns past n are the identity's.  Lane
-    // k of a 64-column chunk keeps x_k in registers; the row's x_i is the
-    // same for the whole wave.
-    for (int k0c = 0; k0c < ld; k0c += 64) {
-        const int k = k0c + lane;
-        double xk[kGphMaxP];
-#pragma unroll
-        for (int d = 0; d < kGphMaxP; ++d) xk[d] = (d < p && k < n) ? a.X[k * p + d] : 0.0;
-        for (int i = k0c + wave; i < ld; i += kGphBigWaves) {
-            if (k > i) continue;
-            double v;
-            if (i < n && k < n) {
-                double r2 = 0.0;
-#pragma unroll
-                for (int d = 0; d < kGphMaxP; ++d) {
-                    if (d < p) {
-                        const double e = a.X[i * p + d] - xk[d];
-                        r2 = fma(e, e, r2);
-                    }
-                }
-                v = tau2 * exp(-lam2 * r2) + (i == k ? s2 : 0.0);
-            } else {
-                v = i == k ? 1.0 : 0.0;
-            }
-            slot[(size_t)i * ld + k] = v;
-        }
-    }
-    for (int i = tid; i < ld; i += blockDim.x) yv[i] = i < n ? a.y[i] : 0.0;
-    if (tid < 3) red[tid] = 0.0;
-    __syncthreads();
-    for (int k0 = 0; k0 < ld; k0 += 32) {
-        const int m = ld - k0 - 32;  // rows below the panel's diagonal block
-        // (a) the diagonal block by wave 0, in registers: lane r < 32 holds
-        //     row r; column entries of other rows come by lane broadcast
-        if (wave == 0) {
-            double dr[32];
-#pragma unroll
-            for (int c = 0; c < 32; ++c)
-                dr[c] = (lane < 32 && c <= lane) ? slot[(size_t)(k0 + lane) * ld + k0 + c] : 0.0;
-            double ld_acc = 0.0, yr = lane < 32 ? yv[k0 + lane] : 0.0, q = 0.0;
-            bool bad = false;
-#pragma unroll
-            for (int j = 0; j < 32; ++j) {
-                const double djj = rl(dr[j], j);
-                bad = bad || !(djj > 0.0);
-                const double ljj = sqrt(djj), r = 1.0 / ljj;
-                ld_acc += log(ljj);
-                const double zj = rl(yr, j) * r;  // forward solve inside the block
-                q += zj * zj;
-                dr[j] = lane > j ? dr[j] * r : (lane == j ? ljj : dr[j]);  // L_rj
-                if (lane > j) yr = fma(-dr[j], zj, yr);
-#pragma unroll
-                for (int c = j + 1; c < 32; ++c) {
-                    const double lcj = rl(dr[j], c);
-                    if (lane >= c) dr[c] = fma(-dr[j], lcj, dr[c]);
-                }
-                if (lane == j) {
-                    rinv[j] = r;
-                    yv[k0 + j] = zj;  // z_j, read by the rows below
-                }
-            }
-            if (lane < 32) {
-#pragma unroll
-                for (int c = 0; c < 32; ++c) Ds[lane * 33 + c] = dr[c];
-            }
-            if (lane == 0) {
-                red[0] += ld_acc;
-                red[1] += q;
-                if (bad) red[2] = 1.0;
-            }
-        }
-        __syncthreads();
-        if (red[2] != 0.0) return -INFINITY;  // block-uniform
-        // (b) the rows below: L_it = (C_it - sum_{s<t} L_is L_ts) / L_tt, right-looking
-        //     within the row; y_i -= sum_t L_it z_t
-        for (int r = tid; r < m; r += blockDim.x) {
-            const int i = k0 + 32 + r;
-            double v[32];
-            const double* src = slot + (size_t)i * ld + k0;
-#pragma unroll
-            for (int t = 0; t < 32; ++t) v[t] = src[t];
-            double yi = yv[i];
-#pragma unroll
-            for (int t = 0; t < 32; ++t) {
-                v[t] *= rinv[t];
-#pragma unroll
-                for (int u = t + 1; u < 32; ++u) v[u] = fma(-v[t], Ds[u * 33 + t], v[u]);
-                yi = fma(-v[t], yv[k0 + t], yi);
-                Lp[(size_t)t * pr + r] = v[t];
-            }
-            yv[i] = yi;
-        }
-        __syncthreads();
-        // (c) trailing triangle, 32 x 32 tiles (bi >= bj), a 4 x 4 block per lane
-        const int nb = m / 32, ntile = nb * (nb + 1) / 2;
-        const int a4 = 4 * (lane >> 3), b4 = 4 * (lane & 7);
-        for (int tI = wave; tI < ntile; tI += kGphBigWaves) {
-            int bi = (int)((sqrt(8.0 * tI + 1.0) - 1.0) * 0.5);
-            while ((bi + 1) * (bi + 2) / 2 <= tI) ++bi;
-            while (bi * (bi + 1) / 2 > tI) --bi;
-            const int bj = tI - bi * (bi + 1) / 2;
-            const int r0 = 32 * bi + a4, c0 = 32 * bj + b4;
-            if (bi == bj && c0 > r0 + 3) continue;  // wholly above the diagonal
-            double acc[4][4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int w = 0; w < 4; ++w) acc[u][w] = slot[(size_t)(k0 + 32 + r0 + u) * ld + k0 + 32 + c0 + w];
-#pragma unroll 4
-            for (int t = 0; t < 32; ++t) {
-                const double* lt = Lp + (size_t)t * pr;
-                double li[4], lj[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    li[u] = lt[r0 + u];
-                    lj[u] = lt[c0 + u];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) acc[u][w] = fma(-li[u], lj[w], acc[u][w]);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int w = 0; w < 4; ++w)
-                    if (c0 + w <= r0 + u) slot[(size_t)(k0 + 32 + r0 + u) * ld + k0 + 32 + c0 + w] = acc[u][w];
-        }
-        __syncthreads();
-    }
-    return -0.5 * red[1] - red[0];
-}
-
-__device__ __forceinline__ int gph_block_next_chain(unsigned long long* q, unsigned long long base, int m, int* sh)
+__device__ __forceinline__ int gph_next_chain(unsigned long long* q, unsigned long long base, int m, int* sh)
 {
     __syncthreads();  // the previous chain's reads of *sh are done
     if (threadIdx.x == 0) {
@@ -490,66 +514,85 @@ __device__ __forceinline__ int gph_block_next_chain(unsigned long long* q, unsig
         *sh = off < (unsigned long long)m ? (int)off : m;
     }
     __syncthreads();
-    return *sh;
+    return uni(*sh);
 }
 
-// The block forms of gph_kernel and gph_init_kernel (n > 96).
-__global__ __launch_bounds__(64 * kGphBigWaves) void gph_big_kernel(GphK a, unsigned long long* q, unsigned long long base, int mode,
-                                                      uint32_t draw)
+// mode 0: FSM (to tstop or through the budget); mode 1: one draw of the
+// synchronized runtime (tstop = draw + 1), recording its largest count;
+// mode 2: vmap padding of draw `draw`.
+template <int NW, bool LEAD>
+__global__ __launch_bounds__(64 * NW, NW >= 8 ? 2 : 4) void gph_kernel(GphK a, unsigned long long* q,
+                                                                      unsigned long long base, int mode, uint32_t draw)
 {
-    extern __shared__ double gsm[];
+    __shared__ __align__(16) double sm[gph_lds_doubles<NW>()];
     __shared__ int s_chain;
-    double* slot = a.slots + (size_t)blockIdx.x * a.ld * a.ld;
+    __shared__ GphState S;
+    double* slot = LEAD ? a.slots + (size_t)blockIdx.x * a.slot_tiles * kGphTile : nullptr;
     const int tid = threadIdx.x;
-    auto ll = [&](const double* tp) { return gph_loglik_big(a, tp, slot, gsm); };
-    unsigned long long steps = 0, padded = 0;
+    unsigned long long steps = 0;
     uint32_t guard = 0;
     for (;;) {
-        const int c = gph_block_next_chain(q, base, a.m, &s_chain);
+        const int c = gph_next_chain(q, base, a.m, &s_chain);
         if (c >= a.m) break;
-        if (mode == 2) {
-            const int reps = a.maxN[draw] - a.counts[(size_t)c * a.n + draw];
-            double th[3], acc = 0.0;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) th[d] = a.th[(size_t)c * 3 + d];
-            for (int r = 0; r < reps; ++r) acc += ll(th);
-            if (reps > 0 && tid == 0) a.sink[c] = acc;
-            padded += (unsigned long long)max(reps, 0);
-            continue;
+        uint32_t stop = a.tstop, t0 = 0;
+        int reps = 0;  // mode 2: likelihoods to discard
+        if (tid == 0) {
+            gph_load(a, c, S);
+            t0 = S.t;
+            if (mode == 2) reps = a.maxN[draw] - a.counts[(size_t)c * a.n + draw];
         }
-        GphState S;
-        gph_load(a, c, S);
-        const uint32_t stop = mode == 1 ? draw + 1 : a.tstop;
-        if (S.t >= stop) continue;
-        const uint32_t t0 = S.t;
-        int64_t budget = a.budget[c];
-        while (S.t < stop && budget > 0) {
-            (void)gph_step(a, c, S, ll, tid, &guard);
-            ++steps;
-            --budget;
+        if (mode == 1) stop = draw + 1;
+        double sum = 0.0;
+        for (;;) {
+            if (tid < 64) {
+                if (tid == 0) S.go = mode == 2 ? (reps-- > 0 ? 1 : 0) : (S.t < stop && S.budget > 0 ? 1 : 0);
+                if (uni(S.go)) {
+                    if (mode != 2)
+                        gph_propose(a, c, S, tid);
+                    else if (tid < 3)
+                        S.tp[tid] = S.th[tid];
+                }
+            }
+            __syncthreads();
+            if (!uni(S.go)) break;
+            const double tp[3] = {uni(S.tp[0]), uni(S.tp[1]), uni(S.tp[2])};
+            const double lp = gph_loglik<NW, LEAD>(a, tp, slot, sm);
+            if (tid == 0) {
+                ++steps;
+                if (mode == 2)
+                    sum += lp;
+                else
+                    gph_decide(a, c, S, lp, &guard);
+            }
         }
-        __syncthreads();  // every thread has read the chain's state before it is stored
-        gph_store(a, c, S, tid);
-        if (tid == 0) a.budget[c] = budget;
-        if (mode == 1 && tid == 0 && S.t > t0) atomicMax(&a.maxN[t0], a.counts[(size_t)c * a.n + t0]);
+        if (tid == 0) {
+            if (mode == 2) {
+                a.sink[c] = sum;
+            } else if (S.t > t0 || S.budget < a.budget[c]) {
+                gph_store(a, c, S);
+                if (mode == 1 && S.t > t0) atomicMax(&a.maxN[t0], a.counts[(size_t)c * a.n + t0]);
+            }
+        }
     }
     if (tid == 0) {
-        if (steps) atomicAdd(&a.ctr[0], steps);
-        if (padded) atomicAdd(&a.ctr[1], padded);
+        if (steps) atomicAdd(&a.ctr[mode == 2 ? 1 : 0], steps);
         if (guard) atomicAdd(&a.ctr[2], (unsigned long long)guard);
     }
 }
 
-__global__ __launch_bounds__(64 * kGphBigWaves) void gph_big_init_kernel(GphK a, int has_x0)
+// Starting state: theta (from x0 or a prior draw N(0, I) on the INIT stream)
+// and its log-likelihood, one block per chain.
+template <int NW, bool LEAD>
+__global__ __launch_bounds__(64 * NW, NW >= 8 ? 2 : 4) void gph_init_kernel(GphK a, int has_x0)
 {
-    extern __shared__ double gsm[];
-    double* slot = a.slots + (size_t)blockIdx.x * a.ld * a.ld;
+    __shared__ __align__(16) double sm[gph_lds_doubles<NW>()];
+    double* slot = LEAD ? a.slots + (size_t)blockIdx.x * a.slot_tiles * kGphTile : nullptr;
     for (int c = blockIdx.x; c < a.m; c += gridDim.x) {
         double th[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d)
-            th[d] = has_x0 ? a.th[(size_t)c * 3 + d] : normal_at<double>(a.seed, (uint32_t)c, 0, ROLE_INIT, 0, (uint32_t)d);
-        const double lx = gph_loglik_big(a, th, slot, gsm);
+            th[d] = has_x0 ? uni(a.th[(size_t)c * 3 + d]) : normal_at<double>(a.seed, (uint32_t)c, 0, ROLE_INIT, 0, (uint32_t)d);
+        const double lx = gph_loglik<NW, LEAD>(a, th, slot, sm);
         __syncthreads();
         if (threadIdx.x == 0) {
 #pragma unroll
@@ -561,6 +604,13 @@ __global__ __launch_bounds__(64 * kGphBigWaves) void gph_big_init_kernel(GphK a,
 }
 
 // ------------------------------------------------------------ host side
+// Tiles of a block's slot: the leading R - 16 tile columns, all R rows each.
+static int gph_slot_tiles(int N)
+{
+    const int R = (N + 16) / 16;
+    return N < 256 ? 0 : (R - 16) * R;
+}
+
 static GphK gph_view(const JobDev& j)
 {
     GphK a;
@@ -571,8 +621,8 @@ static GphK gph_view(const JobDev& j)
     a.tstop = j.tstop;
     a.seed = j.seed;
     a.jitter = j.noise_sd;
-    a.X = (const double*)j.X;
     a.y = (const double*)j.y;
+    a.r2 = (const double*)j.L;
     a.th = (double*)j.x;
     a.nu = (double*)j.V;
     a.lx = (double*)j.lx;
@@ -590,58 +640,66 @@ static GphK gph_view(const JobDev& j)
     a.maxN = j.maxN;
     a.sink = (double*)j.sink;
     a.slots = (double*)j.gslot;
-    a.ld = (j.N + 31) / 32 * 32;
+    a.slot_tiles = gph_slot_tiles(j.N);
     return a;
 }
 
-static bool gph_big(const JobDev& j) { return j.N > kGphMaxN; }
-
-int gph_max_obs() { return kGphBigMaxN; }
+int gph_max_obs() { return kGphMaxN; }
 int gph_max_inputs() { return kGphMaxP; }
 
-static size_t gph_lds_bytes(const JobDev& j)
-{
-    if (gph_big(j)) return 8 * gph_big_lds_doubles((j.N + 31) / 32 * 32);
-    return 8 * ((size_t)((j.N * j.pdim + 1) & ~1) + (size_t)j.N * (j.N + 1) / 2 + (size_t)j.N);
-}
+// Waves per block by observations: 2 NW tile rows of 16 must hold them and y's
+// row; 8 waves are the most whose tiles fit the registers (17 tiles = 136 of
+// 256 per lane), and from 256 observations on the leading columns go through
+// memory.
+static int gph_waves(int N) { return N < 32 ? 1 : (N < 64 ? 2 : (N < 128 ? 4 : 8)); }
 
-static int gph_cus()
+#define FSMMC_GPH_DISPATCH(N_, CALL)    \
+    switch (gph_waves(N_)) {           \
+    case 1: CALL(1, false); break;     \
+    case 2: CALL(2, false); break;     \
+    case 4: CALL(4, false); break;     \
+    default:                           \
+        if ((N_) < 256) {              \
+            CALL(8, false);            \
+        } else {                       \
+            CALL(8, true);             \
+        }                              \
+    }
+
+// Blocks of the persistent kernel: what the chip holds at once, at most one per chain.
+static hipError_t gph_blocks(const JobDev& j, int* blocks)
 {
-    int cus = 256, dev = 0, v = 0;
+    int cus = 256, dev = 0, v = 0, per_cu = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
         cus = v;
-    return cus;
+    hipError_t e = hipSuccess;
+#define FSMMC_GPH_OCC(NW, LEAD) \
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)gph_kernel<NW, LEAD>, 64 * NW, 0)
+    FSMMC_GPH_DISPATCH(j.N, FSMMC_GPH_OCC)
+#undef FSMMC_GPH_OCC
+    *blocks = std::max(1, std::min(j.m, cus * std::max(1, per_cu)));
+    return e;
 }
 
-static int gph_blocks(const JobDev& j)
+size_t gph_slot_bytes(const JobDev& j) { return (size_t)j.pblocks * gph_slot_tiles(j.N) * kGphTile * 8; }
+
+size_t gph_dist_bytes(int N)
 {
-    const size_t lds = gph_lds_bytes(j);
-    const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(16, (160 * 1024) / std::max<size_t>(lds, 1)));
-    return std::max(1, std::min(j.m, gph_cus() * per_cu));
+    const size_t R = (size_t)(N + 16) / 16;
+    return R * (R + 1) / 2 * kGphTile * 8;
 }
 
-size_t gph_slot_bytes(const JobDev& j)
+// Launch shape, and the squared distances (into j.L, after X is in place).
+hipError_t gph_setup(JobDev& j, hipStream_t s)
 {
-    if (!gph_big(j)) return 0;
-    const size_t ld = (size_t)(j.N + 31) / 32 * 32;
-    return (size_t)gph_blocks(j) * ld * ld * 8;
-}
-
-hipError_t gph_setup(JobDev& j)
-{
-    const size_t lds = gph_lds_bytes(j);
-    if (lds > 160 * 1024) return hipErrorInvalidValue;
-    if (lds > 64 * 1024) {
-        const void* k0 = gph_big(j) ? (const void*)gph_big_kernel : (const void*)gph_kernel;
-        const void* k1 = gph_big(j) ? (const void*)gph_big_init_kernel : (const void*)gph_init_kernel;
-        hipError_t e = hipFuncSetAttribute(k0, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e == hipSuccess) e = hipFuncSetAttribute(k1, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    j.pblocks = gph_blocks(j);
-    j.pwpb = gph_big(j) ? kGphBigWaves : 1;
-    return hipSuccess;
+    j.pwpb = gph_waves(j.N);
+    hipError_t e = gph_blocks(j, &j.pblocks);
+    if (e != hipSuccess) return e;
+    const int R = (j.N + 16) / 16;
+    hipLaunchKernelGGL(gph_dist_kernel, dim3(R * (R + 1) / 2), dim3(256), 0, s, (const double*)j.X, j.N, j.pdim,
+                       (double*)j.L);
+    return hipGetLastError();
 }
 
 hipError_t gph_init_state(const JobDev& j, const void* x0, hipStream_t s)
@@ -650,21 +708,20 @@ hipError_t gph_init_state(const JobDev& j, const void* x0, hipStream_t s)
         hipError_t e = hipMemcpyAsync(j.x, x0, (size_t)j.m * 3 * 8, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) return e;
     }
-    if (gph_big(j))
-        hipLaunchKernelGGL(gph_big_init_kernel, dim3(j.pblocks), dim3(64 * kGphBigWaves), gph_lds_bytes(j), s, gph_view(j), x0 ? 1 : 0);
-    else
-        hipLaunchKernelGGL(gph_init_kernel, dim3(j.pblocks), dim3(64), gph_lds_bytes(j), s, gph_view(j), x0 ? 1 : 0);
+#define FSMMC_GPH_INIT(NW, LEAD) \
+    hipLaunchKernelGGL((gph_init_kernel<NW, LEAD>), dim3(j.pblocks), dim3(64 * NW), 0, s, gph_view(j), x0 ? 1 : 0)
+    FSMMC_GPH_DISPATCH(j.N, FSMMC_GPH_INIT)
+#undef FSMMC_GPH_INIT
     return hipGetLastError();
 }
 
 hipError_t gph_run(const JobDev& j, int mode, uint32_t draw, unsigned long long* ticket, hipStream_t s)
 {
-    if (gph_big(j))
-        hipLaunchKernelGGL(gph_big_kernel, dim3(j.pblocks), dim3(64 * kGphBigWaves), gph_lds_bytes(j), s, gph_view(j),
-                           (unsigned long long*)j.queue, *ticket, mode, draw);
-    else
-        hipLaunchKernelGGL(gph_kernel, dim3(j.pblocks), dim3(64), gph_lds_bytes(j), s, gph_view(j),
-                           (unsigned long long*)j.queue, *ticket, mode, draw);
+#define FSMMC_GPH_RUN(NW, LEAD)                                                                             \
+    hipLaunchKernelGGL((gph_kernel<NW, LEAD>), dim3(j.pblocks), dim3(64 * NW), 0, s, gph_view(j),           \
+                       (unsigned long long*)j.queue, *ticket, mode, draw)
+    FSMMC_GPH_DISPATCH(j.N, FSMMC_GPH_RUN)
+#undef FSMMC_GPH_RUN
     *ticket += (unsigned long long)j.m + (unsigned long long)j.pblocks;
     return hipGetLastError();
 }
