@@ -22,6 +22,8 @@
 #include "fsmmc_device.h"
 #include "fsmmc_internal.h"
 
+#include <utility>
+
 namespace fsmmc {
 
 constexpr int kGphMaxN = 512;  // observations
@@ -115,20 +117,60 @@ __device__ __forceinline__ d4 tile_mac(const d4& a, const d4& b, d4 acc)
     return acc;
 }
 
-// What a wave gathers along the way: pivots as mantissa product and exponent
-// sum (lanes 0-15), |z|^2 (the lanes of row n), a pivot that was not positive.
+// v[k] / v[k] = x for a wave-uniform k known at run time only (registers have no
+// index: a chain of uniform branches).  The code of a factorisation has to
+// stay small: straight-line copies per tile (a 64 KiB instruction cache serves
+// two CUs) ran four times slower than these loops.
+// Every index into a register tile array is a template constant (each):
+// with unrolled loops the branches are merged into one indexed access before
+// the loops unroll, and the array ends up in scratch memory.
+#define FSMMC_INLINE __attribute__((always_inline))
+template <int... I, typename F>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, const F& f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void each(const F& f)
+{
+    each_of(std::make_integer_sequence<int, N>{}, f);
+}
+template <int N>
+__device__ __forceinline__ d4 pick(const d4 (&v)[N], int k)
+{
+    d4 x = v[0];
+    each<N>([&](auto i) FSMMC_INLINE {
+        if (i == k) x = v[i];
+    });
+    return x;
+}
+template <int N>
+__device__ __forceinline__ void put(d4 (&v)[N], int k, const d4& x)
+{
+    each<N>([&](auto i) FSMMC_INLINE {
+        if (i == k) v[i] = x;
+    });
+}
+
+// What a wave gathers along the way: the pivots of its diagonal tiles as a
+// mantissa product (at most 64 factors in [1/2, 1)) and an exponent sum, and
+// |z|^2 (the lanes of row n).  A pivot that is not positive makes its column,
+// and with it z, NaN.
 struct GphSum {
     double pm = 1.0, zz = 0.0;
-    int pe = 0, bad = 0;
+    int pe = 0;
 };
 
 // The diagonal tile: acc = minus the remaining tile.  Lanes 0-15 take the
-// tile's rows whole, lanes 16-31 the identity's: eliminating its first nc
-// columns leaves L in the former and L^-T in the latter, and minus L^-1 goes to
-// inv as a tile.  yrow: the tile's row that is row n of the matrix, or -1.
+// tile's rows whole, lanes 16-31 the identity's: eliminating the columns
+// leaves L in the former and L^-T in the latter, and minus L^-1 goes to inv as
+// a tile.  Only the first nc columns exist (the last tile; what the others
+// hold goes nowhere).  yrow: the tile's row that is row n of the matrix, or -1.
 __device__ __forceinline__ void gph_factor(const d4& acc, int nc, int yrow, int lane, double* inv, GphSum& G)
 {
-    const int i = lane & 15;
+    __builtin_amdgcn_s_setprio(3);  // every other wave of the block waits for this one
+    int i = lane & 15;
+    asm volatile("" : "+v"(i));
     const bool unit = (lane & 16) != 0;
     double W[16];
 #pragma unroll
@@ -140,35 +182,36 @@ __device__ __forceinline__ void gph_factor(const d4& acc, int nc, int yrow, int 
 #pragma unroll
         for (int q = 0; q < 4; ++q) W[4 * r + q] = unit ? (4 * r + q == i ? 1.0 : 0.0) : c[q];
     }
-    double piv = 1.0;
+    auto pivot = [&](double ajj, int j) {
+        G.pm *= j < nc ? __builtin_amdgcn_frexp_mant(ajj) : 1.0;
+        G.pe += j < nc ? __builtin_amdgcn_frexp_exp(ajj) : 0;
+        // 1 / sqrt(ajj): the hardware estimate (about 2^-26) and one
+        // third-order step, y + y e (1/2 + 3/8 e), e = 1 - a y^2
+        const double y0 = __builtin_amdgcn_rsq(ajj);
+        const double e = fma(-(ajj * y0), y0, 1.0);
+        return fma(y0 * e, fma(0.375, e, 0.5), y0);
+    };
+    double r = pivot(rl(W[0], 0), 0);
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-        if (j < nc) {
-            const double ajj = rl(W[j], j);
-            G.bad |= !(ajj > 0.0);
-            // 1 / sqrt(ajj): the hardware estimate (about 2^-26) and one
-            // third-order step, y + y e (1/2 + 3/8 e), e = 1 - a y^2
-            const double y0 = __builtin_amdgcn_rsq(ajj);
-            const double e = fma(-(ajj * y0), y0, 1.0);
-            const double r = fma(y0 * e, fma(0.375, e, 0.5), y0);
-            if (lane == j) piv = ajj;
-            W[j] *= r;
-#pragma unroll
-            for (int u = j + 1; u < 16; ++u) W[u] = fma(-W[j], rl(W[j], u), W[u]);
-            __builtin_amdgcn_sched_barrier(0);  // one column's lane reads in scalar registers at a time
+        W[j] *= r;
+        if (j < 15) {  // the next pivot first: its reciprocal root runs under the other updates
+            W[j + 1] = fma(-W[j], rl(W[j], j + 1), W[j + 1]);
+            r = pivot(rl(W[j + 1], j + 1), j + 1);
         }
+#pragma unroll
+        for (int u = j + 2; u < 16; ++u) W[u] = fma(-W[j], rl(W[j], u), W[u]);
+        __builtin_amdgcn_sched_barrier(0);  // one column's lane reads in scalar registers at a time
     }
-    G.pm *= __builtin_amdgcn_frexp_mant(piv);
-    G.pe += __builtin_amdgcn_frexp_exp(piv);
     if (lane == yrow) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if (j < nc) G.zz = fma(W[j], W[j], G.zz);
+        for (int j = 0; j < 16; ++j) G.zz = j < nc ? fma(W[j], W[j], G.zz) : G.zz;
     }
     if (unit && lane < 32) {  // lane 16 + i: column i of L^-1, element u at (row u, column i)
 #pragma unroll
         for (int u = 0; u < 16; ++u) inv[((i >> 3) * 64 + (i & 3) * 16 + u) * 2 + ((i >> 2) & 1)] = -W[u];
     }
+    __builtin_amdgcn_s_setprio(0);
 }
 
 // Minus tile (I, J) of C (with y as row n).
@@ -189,16 +232,19 @@ __device__ __forceinline__ d4 gph_tile_of_c(const GphK& a, double tau2, double l
     return v;
 }
 
-// LDS doubles: the published column (2 NW tiles), the inverse, three sums per wave
+// LDS doubles: the published column (2 NW tiles), the inverse, two sums per wave
 template <int NW>
-constexpr int gph_lds_doubles() { return (2 * NW + 1) * kGphTile + 3 * NW; }
+constexpr int gph_lds_doubles() { return (2 * NW + 1) * kGphTile + 2 * NW; }
 
 template <int NW, bool LEAD>
 __device__ double gph_loglik(const GphK& a, const double* th, double* slot, double* sm)
 {
     constexpr int RW = 2 * NW;
     const int n = a.N, T = (n + 15) >> 4, R = (n + 16) >> 4, yrow = n & 15;
-    const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
+    int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
+    // opaque here and at each phase below: what is derived from them would
+    // otherwise be kept across the whole chain loop, and spilled
+    asm volatile("" : "+v"(lane), "+s"(wave));
     double* colb = sm;
     double* inv = sm + RW * kGphTile;
     double* red = inv + kGphTile;
@@ -218,68 +264,69 @@ __device__ double gph_loglik(const GphK& a, const double* th, double* slot, doub
         auto at = [&](int I, int k) { return slot + (size_t)(k * R + I) * kGphTile; };
         for (int P = 0; P < base; P += 4) {
             const int pc = min(4, base - P);
-            d4 acc[4][4];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int rel = wave + NW * s, I = P + rel;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    acc[s][c] = I < R && c < pc && c <= rel ? gph_tile_of_c(a, tau2, lam2, s2, I, P + c, lane)
-                                                            : d4{0.0, 0.0, 0.0, 0.0};
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+            d4 acc[4][4];  // [slot s: row P + wave + NW s][column]
+            // C's tiles by way of the places in the slot that their L will take
+#pragma unroll 1
+            for (int v = 0; v < 16; ++v) {
+                const int rel = wave + NW * (v >> 2), c = v & 3;
+                if (P + rel < R && c < pc && c <= rel)
+                    tile_store(at(P + rel, P + c), lane, gph_tile_of_c(a, tau2, lam2, s2, P + rel, P + c, lane));
             }
+            each<16>([&](auto v) FSMMC_INLINE {
+                const int rel = wave + NW * (v >> 2), c = v & 3;
+                acc[v >> 2][v & 3] =
+                    P + rel < R && c < pc && c <= rel ? tile_load(at(P + rel, P + c), lane) : d4{0.0, 0.0, 0.0, 0.0};
+            });
             for (int k = 0; k < P; ++k) {
                 d4 A[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) A[c] = tile_load(at(P + min(c, pc - 1), k), lane);
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
+                each<4>([&](auto c) FSMMC_INLINE { A[c] = tile_load(at(P + min((int)c, pc - 1), k), lane); });
+                each<4>([&](auto s) FSMMC_INLINE {
                     const int I = P + wave + NW * s;
-                    if (I >= R) continue;
-                    const d4 B = tile_load(at(I, k), lane);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) acc[s][c] = tile_mac(A[c], B, acc[s][c]);
-                }
+                    if (I < R) {
+                        const d4 B = tile_load(at(I, k), lane);
+                        each<4>([&](auto c) FSMMC_INLINE { acc[s][c] = tile_mac(A[c], B, acc[s][c]); });
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
             }
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                if (t >= pc) break;
-                if (wave == t) gph_factor(acc[0][t], 16, -1, lane, inv, G);
+#pragma unroll 1
+            for (int t = 0; t < pc; ++t) {
+                asm volatile("" : "+v"(lane), "+s"(wave));
+                if (wave == t) gph_factor(pick(acc[0], t), 16, -1, lane, inv, G);
                 __syncthreads();
                 const d4 iv = tile_load(inv, lane);
                 d4 L[4];
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
+                each<4>([&](auto s) FSMMC_INLINE {
                     const int rel = wave + NW * s, I = P + rel;
+                    L[s] = d4{0.0, 0.0, 0.0, 0.0};
                     if (rel > t && I < R) {
-                        L[s] = solve(iv, acc[s][t], I);
+                        L[s] = solve(iv, pick(acc[s], t), I);
                         tile_store(at(I, P + t), lane, L[s]);
                         if (rel < pc) tile_store(colb + rel * kGphTile, lane, L[s]);
                     }
-                }
+                });
                 __syncthreads();
-#pragma unroll
-                for (int u = t + 1; u < 4; ++u) {
-                    if (u >= pc) break;
-                    const d4 A = tile_load(colb + u * kGphTile, lane);
-#pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        if (wave + NW * s >= u && P + wave + NW * s < R) acc[s][u] = tile_mac(A, L[s], acc[s][u]);
-                }
+                each<4>([&](auto u) FSMMC_INLINE {
+                    if (u > t && u < pc) {
+                        const d4 A = tile_load(colb + u * kGphTile, lane);
+                        each<4>([&](auto s) FSMMC_INLINE {
+                            if (wave + NW * s >= u && P + wave + NW * s < R)
+                                acc[s][u] = tile_mac(A, L[s], acc[s][u]);
+                        });
+                    }
+                });
             }
         }
     }
     // the trailing rows base .. R - 1, all tiles in registers
     const int ra = wave, rb = RW - 1 - wave;  // this wave's rows, relative to base
-    const bool hasa = base + ra < R, hasb = base + rb < R;
     d4 acc[RW + 1];
-#pragma unroll
+    each<RW + 1>([&](auto p) FSMMC_INLINE { acc[p] = d4{0.0, 0.0, 0.0, 0.0}; });
+#pragma unroll 1
     for (int p = 0; p <= RW; ++p) {
         const bool second = p > wave;
         const int I = base + (second ? rb : ra), J = base + (second ? RW - p : p);
-        acc[p] = I < R && J < T ? gph_tile_of_c(a, tau2, lam2, s2, I, J, lane) : d4{0.0, 0.0, 0.0, 0.0};
-        __builtin_amdgcn_sched_barrier(0);  // one tile's exponentials at a time (registers)
+        if (I < R && J < T) put(acc, p, gph_tile_of_c(a, tau2, lam2, s2, I, J, lane));
     }
     if constexpr (LEAD) {
         // minus the leading columns' products: column k of the finished tiles
@@ -299,80 +346,70 @@ __device__ double gph_loglik(const GphK& a, const double* th, double* slot, doub
             __syncthreads();
             if (k + 1 < base) fetch(k + 1);
             const d4 La = tile_load(colb + ra * kGphTile, lane), Lb = tile_load(colb + rb * kGphTile, lane);
-#pragma unroll
-            for (int p = 0; p <= RW; ++p) {
+            each<RW + 1>([&](auto p) FSMMC_INLINE {
                 const bool second = p > wave;
                 const d4 A = tile_load(colb + (second ? RW - p : p) * kGphTile, lane);
                 if (second)
                     acc[p] = tile_mac(A, Lb, acc[p]);
                 else
                     acc[p] = tile_mac(A, La, acc[p]);
-            }
+                __builtin_amdgcn_sched_barrier(0);
+            });
         }
         __syncthreads();
     }
     const int nt = T - base;
+#pragma unroll 1
     for (int t = 0; t < nt; ++t) {
+        asm volatile("" : "+v"(lane), "+s"(wave));
+        const int ra = wave, rb = RW - 1 - wave;
+        const bool hasa = base + ra < R, hasb = base + rb < R;
         if (wave == (t < NW ? t : RW - 1 - t)) {  // the owner of row t: its diagonal tile is at position w or w + 1
-            d4 d = acc[0];
-            const int pd = t < NW ? wave : wave + 1;
-#pragma unroll
-            for (int p = 1; p <= RW; ++p)
-                if (p == pd) d = acc[p];
             const bool last = base + t == R - 1;
-            gph_factor(d, min(16, n - 16 * (base + t)), last ? yrow : -1, lane, inv, G);
+            gph_factor(pick(acc, t < NW ? wave : wave + 1), min(16, n - 16 * (base + t)), last ? yrow : -1, lane, inv, G);
         }
         __syncthreads();
         const d4 iv = tile_load(inv, lane);
         d4 La = d4{0.0, 0.0, 0.0, 0.0}, Lb = La;
         if (ra > t && hasa) {
-            d4 x = acc[0];
-#pragma unroll
-            for (int p = 1; p < NW; ++p)
-                if (p == t) x = acc[p];
-            La = solve(iv, x, base + ra);
+            La = solve(iv, pick(acc, t), base + ra);
             tile_store(colb + ra * kGphTile, lane, La);
         }
         if (rb > t && hasb) {
-            d4 x = acc[RW];
-#pragma unroll
-            for (int p = 1; p < RW; ++p)
-                if (p == t) x = acc[RW - p];
-            Lb = solve(iv, x, base + rb);
+            Lb = solve(iv, pick(acc, RW - t), base + rb);
             tile_store(colb + rb * kGphTile, lane, Lb);
         }
         __syncthreads();
-#pragma unroll
-        for (int p = 0; p <= RW; ++p) {
+        each<RW + 1>([&](auto p) FSMMC_INLINE {
             const bool second = p > wave;
             const int c = second ? RW - p : p;
-            if (c <= t || base + c >= T || !(second ? hasb : hasa)) continue;
-            const d4 A = tile_load(colb + c * kGphTile, lane);
-            if (second)
-                acc[p] = tile_mac(A, Lb, acc[p]);
-            else
-                acc[p] = tile_mac(A, La, acc[p]);
-        }
+            if (c > t && base + c < T && (second ? hasb : hasa)) {
+                const d4 A = tile_load(colb + c * kGphTile, lane);
+                if (second)
+                    acc[p] = tile_mac(A, Lb, acc[p]);
+                else
+                    acc[p] = tile_mac(A, La, acc[p]);
+            }
+        });
     }
     // sums over the lanes, then over the waves in order
-    const double lg = wave_sum(log(G.pm) + (double)G.pe * 0.69314718055994530942);
-    const double zz = wave_sum(G.zz);
-    const int bad = __any(G.bad) ? 1 : 0;
-    if constexpr (NW == 1) return bad ? -INFINITY : -0.5 * zz - 0.5 * lg;
-    if (lane == 0) {
-        red[3 * wave] = lg;
-        red[3 * wave + 1] = zz;
-        red[3 * wave + 2] = bad ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    double slg = 0.0, szz = 0.0, sbad = 0.0;
+    double lg = log(G.pm) + (double)G.pe * 0.69314718055994530942;
+    double zz = wave_sum(G.zz);
+    if constexpr (NW > 1) {
+        if (lane == 0) {
+            red[2 * wave] = lg;
+            red[2 * wave + 1] = zz;
+        }
+        __syncthreads();
+        lg = zz = 0.0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        slg += red[3 * w];
-        szz += red[3 * w + 1];
-        sbad += red[3 * w + 2];
+        for (int w = 0; w < NW; ++w) {
+            lg += red[2 * w];
+            zz += red[2 * w + 1];
+        }
     }
-    return sbad != 0.0 ? -INFINITY : -0.5 * szz - 0.5 * slg;
+    const double v = -0.5 * zz - 0.5 * lg;
+    return v != v ? -INFINITY : v;  // not positive definite
 }
 
 // Squared distances of the inputs, one thread per element of a tile; rows and
@@ -410,11 +447,13 @@ __device__ __forceinline__ void gph_propose(const GphK& a, int c, GphState& S, i
 {
     double nu[3], phi, pmin, pmax, logu = S.logu;
     int evals;
+    const uint64_t seed = (uint64_t)uni((int64_t)a.seed);
+    const uint32_t t = uni(S.t);
     if (uni(S.k) == 1) {  // INIT: direction, threshold, first angle and bracket
 #pragma unroll
-        for (int d = 0; d < 3; ++d) nu[d] = normal_at<double>(a.seed, (uint32_t)c, S.t, ROLE_NU, 0, (uint32_t)d);
-        logu = log(uniform<double>(a.seed, (uint32_t)c, S.t, ROLE_THRESH, 0));
-        phi = 2.0 * 3.14159265358979323846 * uniform<double>(a.seed, (uint32_t)c, S.t, ROLE_ANGLE, 0);
+        for (int d = 0; d < 3; ++d) nu[d] = normal_at<double>(seed, (uint32_t)c, t, ROLE_NU, 0, (uint32_t)d);
+        logu = log(uniform<double>(seed, (uint32_t)c, t, ROLE_THRESH, 0));
+        phi = 2.0 * 3.14159265358979323846 * uniform<double>(seed, (uint32_t)c, t, ROLE_ANGLE, 0);
         pmin = phi - 2.0 * 3.14159265358979323846;
         pmax = phi;
         evals = 0;
@@ -425,7 +464,7 @@ __device__ __forceinline__ void gph_propose(const GphK& a, int c, GphState& S, i
         pmin = phi < 0.0 ? phi : S.pmin;
         pmax = phi < 0.0 ? S.pmax : phi;
         evals = S.evals;
-        phi = pmin + (pmax - pmin) * uniform<double>(a.seed, (uint32_t)c, S.t, ROLE_ANGLE, (uint32_t)evals);
+        phi = pmin + (pmax - pmin) * uniform<double>(seed, (uint32_t)c, t, ROLE_ANGLE, (uint32_t)evals);
     }
     const double cs = cos(phi), sn = sin(phi);
     if (lane == 0) {
@@ -527,6 +566,10 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 2 : 4) void gph_kernel(GphK a, u
     __shared__ __align__(16) double sm[gph_lds_doubles<NW>()];
     __shared__ int s_chain;
     __shared__ GphState S;
+    // the FSM part reads its arguments from LDS, wave 0 only: kept in scalar
+    // registers they would be spilled around every column of gph_factor
+    __shared__ GphK sa;
+    if (threadIdx.x == 0) sa = a;
     double* slot = LEAD ? a.slots + (size_t)blockIdx.x * a.slot_tiles * kGphTile : nullptr;
     const int tid = threadIdx.x;
     unsigned long long steps = 0;
@@ -534,21 +577,20 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 2 : 4) void gph_kernel(GphK a, u
     for (;;) {
         const int c = gph_next_chain(q, base, a.m, &s_chain);
         if (c >= a.m) break;
-        uint32_t stop = a.tstop, t0 = 0;
+        uint32_t t0 = 0;
         int reps = 0;  // mode 2: likelihoods to discard
         if (tid == 0) {
-            gph_load(a, c, S);
+            gph_load(sa, c, S);
             t0 = S.t;
-            if (mode == 2) reps = a.maxN[draw] - a.counts[(size_t)c * a.n + draw];
+            if (mode == 2) reps = sa.maxN[draw] - sa.counts[(size_t)c * sa.n + draw];
         }
-        if (mode == 1) stop = draw + 1;
         double sum = 0.0;
         for (;;) {
             if (tid < 64) {
-                if (tid == 0) S.go = mode == 2 ? (reps-- > 0 ? 1 : 0) : (S.t < stop && S.budget > 0 ? 1 : 0);
+                if (tid == 0) S.go = mode == 2 ? (reps-- > 0 ? 1 : 0) : (S.t < (mode == 1 ? draw + 1 : sa.tstop) && S.budget > 0 ? 1 : 0);
                 if (uni(S.go)) {
                     if (mode != 2)
-                        gph_propose(a, c, S, tid);
+                        gph_propose(sa, c, S, tid);
                     else if (tid < 3)
                         S.tp[tid] = S.th[tid];
                 }
@@ -562,21 +604,21 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 2 : 4) void gph_kernel(GphK a, u
                 if (mode == 2)
                     sum += lp;
                 else
-                    gph_decide(a, c, S, lp, &guard);
+                    gph_decide(sa, c, S, lp, &guard);
             }
         }
         if (tid == 0) {
             if (mode == 2) {
-                a.sink[c] = sum;
-            } else if (S.t > t0 || S.budget < a.budget[c]) {
-                gph_store(a, c, S);
-                if (mode == 1 && S.t > t0) atomicMax(&a.maxN[t0], a.counts[(size_t)c * a.n + t0]);
+                sa.sink[c] = sum;
+            } else if (S.t > t0 || S.budget < sa.budget[c]) {
+                gph_store(sa, c, S);
+                if (mode == 1 && S.t > t0) atomicMax(&sa.maxN[t0], sa.counts[(size_t)c * sa.n + t0]);
             }
         }
     }
     if (tid == 0) {
-        if (steps) atomicAdd(&a.ctr[mode == 2 ? 1 : 0], steps);
-        if (guard) atomicAdd(&a.ctr[2], (unsigned long long)guard);
+        if (steps) atomicAdd(&sa.ctr[mode == 2 ? 1 : 0], steps);
+        if (guard) atomicAdd(&sa.ctr[2], (unsigned long long)guard);
     }
 }
 
