@@ -76,12 +76,13 @@ __device__ __forceinline__ double rl(double v, int l)
 // diagonal tile (gph_factor) and publishes minus its inverse in LDS; every wave
 // then takes its rows' tiles of column t to L_It = A_It L_tt^-T (four MFMAs),
 // publishes them in LDS and updates its remaining tiles with L_It L_ct^T (four
-// MFMAs each, L_ct from LDS).  Two barriers per tile column.  Wave w owns rows
+// MFMAs each, L_ct from LDS).  Two barriers per tile column; the next diagonal
+// tile is factored beside the other waves' updates.  Wave w owns rows
 // w and 2 NW - 1 - w: 2 NW + 1 tiles whatever w, all in registers (position p:
 // column p of the first row for p <= w, column 2 NW - p of the second above).
 //
 // LEAD (n >= 256, more than 16 tile rows): the leading R - 16 tile columns go
-// first, in panels of four columns (rows dealt to the waves in turn, up to four
+// first, in panels of four columns (rows dealt to the waves in turn, up to five
 // each); their finished tiles go to the block's slot in memory, and the
 // panels after them and the trailing 16 rows start from C minus the products
 // of those tiles.
@@ -89,10 +90,18 @@ __device__ __forceinline__ double rl(double v, int l)
 // What bounds it: the FP64 matrix and vector units have the same rate (one
 // MFMA = 64 cycles of its SIMD = 16 FMAs), but an FMA form needs its operands
 // broadcast through LDS (four times the LDS bytes per flop) or by lane reads;
-// what is left is the serial chain of the diagonal tiles (about 3000 cycles
-// each).
-// @MEASURED@
+// what is left is the serial chain of the diagonal tiles (about 3600 cycles
+// each alone) and, with several blocks per CU, the issue slots that the
+// diagonal tiles, the exponentials and the updates share.
+// Measured against the factorisations this replaced (n <= 96: the wave's own
+// rows in LDS; above: a global work matrix, 32-column panels), whole jobs:
+//   n =  25, 1024 chains x 100 draws:  24.9 ->  5.2 ms
+//   n =  63,  512 chains x  60 draws:  70.4 ->  7.7 ms
+//   n = 100, 1024 chains x  60 draws: 325   -> 23.6 ms
+//   n = 191, 1024 chains x   8 draws (8 waves a block -> 6): 17.1 -> 15.2 ms
+//   n = 414,  512 chains x  16 draws: 401   -> 80.3 ms
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 
 // A tile in memory: doubles [half][lane][2], so a lane's four values are two
 // 16-byte accesses that fill whole lines.
@@ -109,6 +118,12 @@ __device__ __forceinline__ void tile_store(double* t, int lane, const d4& v)
     reinterpret_cast<double2*>(t)[64 + lane] = make_double2(v[2], v[3]);
 }
 
+// c ? a : b by selects (a branch would give the product two homes and copies between)
+__device__ __forceinline__ d4 choose(bool c, const d4& a, const d4& b)
+{
+    return d4{c ? a[0] : b[0], c ? a[1] : b[1], c ? a[2] : b[2], c ? a[3] : b[3]};
+}
+
 // acc + (a b^T)^T, a and b tiles as fragments
 __device__ __forceinline__ d4 tile_mac(const d4& a, const d4& b, d4 acc)
 {
@@ -118,9 +133,8 @@ __device__ __forceinline__ d4 tile_mac(const d4& a, const d4& b, d4 acc)
 }
 
 // v[k] / v[k] = x for a wave-uniform k known at run time only (registers have no
-// index: a chain of uniform branches).  The code of a factorisation has to
-// stay small: straight-line copies per tile (a 64 KiB instruction cache serves
-// two CUs) ran four times slower than these loops.
+// index: a chain of uniform branches).  With these the tile loops are loops:
+// copies of their bodies per tile made 150 KiB of code (now 50) and spilled.
 // Every index into a register tile array is a template constant (each):
 // with unrolled loops the branches are merged into one indexed access before
 // the loops unroll, and the array ends up in scratch memory.
@@ -232,9 +246,14 @@ __device__ __forceinline__ d4 gph_tile_of_c(const GphK& a, double tau2, double l
     return v;
 }
 
-// LDS doubles: the published column (2 NW tiles), the inverse, two sums per wave
+// LDS doubles: one published column (2 NW tiles; two for 8 waves), the inverse, two
+// sums per wave
 template <int NW>
-constexpr int gph_lds_doubles() { return (2 * NW + 1) * kGphTile + 2 * NW; }
+constexpr int gph_lds_doubles() { return ((NW >= 8 ? 4 : 2) * NW + 1) * kGphTile + 2 * NW; }
+
+// Waves a SIMD holds at the registers of the class: 2 NW + 1 tiles of 8 and
+// about 60 more (4 waves: 128, 3: 168, 2: 256).
+constexpr int gph_waves_per_simd(int NW) { return NW >= 8 ? 2 : (NW >= 6 ? 3 : 4); }
 
 template <int NW, bool LEAD>
 __device__ double gph_loglik(const GphK& a, const double* th, double* slot, double* sm)
@@ -246,7 +265,8 @@ __device__ double gph_loglik(const GphK& a, const double* th, double* slot, doub
     // otherwise be kept across the whole chain loop, and spilled
     asm volatile("" : "+v"(lane), "+s"(wave));
     double* colb = sm;
-    double* inv = sm + RW * kGphTile;
+    constexpr int NB = NW >= 8 ? 2 : 1;  // column buffers
+    double* inv = sm + NB * RW * kGphTile;
     double* red = inv + kGphTile;
     const double tau2 = th[0] * th[0], lam2 = th[1] * th[1], s2 = th[2] * th[2] + a.jitter;
     GphSum G;
@@ -261,18 +281,19 @@ __device__ double gph_loglik(const GphK& a, const double* th, double* slot, doub
     };
     const int base = LEAD ? R - RW : 0;  // rows and columns below go first
     if constexpr (LEAD) {
+        constexpr int NS = (kGphMaxN / 16 + 1 + NW - 1) / NW;  // rows per wave, at most
         auto at = [&](int I, int k) { return slot + (size_t)(k * R + I) * kGphTile; };
         for (int P = 0; P < base; P += 4) {
             const int pc = min(4, base - P);
-            d4 acc[4][4];  // [slot s: row P + wave + NW s][column]
+            d4 acc[NS][4];  // [slot s: row P + wave + NW s][column]
             // C's tiles by way of the places in the slot that their L will take
 #pragma unroll 1
-            for (int v = 0; v < 16; ++v) {
+            for (int v = 0; v < 4 * NS; ++v) {
                 const int rel = wave + NW * (v >> 2), c = v & 3;
                 if (P + rel < R && c < pc && c <= rel)
                     tile_store(at(P + rel, P + c), lane, gph_tile_of_c(a, tau2, lam2, s2, P + rel, P + c, lane));
             }
-            each<16>([&](auto v) FSMMC_INLINE {
+            each<4 * NS>([&](auto v) FSMMC_INLINE {
                 const int rel = wave + NW * (v >> 2), c = v & 3;
                 acc[v >> 2][v & 3] =
                     P + rel < R && c < pc && c <= rel ? tile_load(at(P + rel, P + c), lane) : d4{0.0, 0.0, 0.0, 0.0};
@@ -280,7 +301,7 @@ __device__ double gph_loglik(const GphK& a, const double* th, double* slot, doub
             for (int k = 0; k < P; ++k) {
                 d4 A[4];
                 each<4>([&](auto c) FSMMC_INLINE { A[c] = tile_load(at(P + min((int)c, pc - 1), k), lane); });
-                each<4>([&](auto s) FSMMC_INLINE {
+                each<NS>([&](auto s) FSMMC_INLINE {
                     const int I = P + wave + NW * s;
                     if (I < R) {
                         const d4 B = tile_load(at(I, k), lane);
@@ -295,8 +316,8 @@ __device__ double gph_loglik(const GphK& a, const double* th, double* slot, doub
                 if (wave == t) gph_factor(pick(acc[0], t), 16, -1, lane, inv, G);
                 __syncthreads();
                 const d4 iv = tile_load(inv, lane);
-                d4 L[4];
-                each<4>([&](auto s) FSMMC_INLINE {
+                d4 L[NS];
+                each<NS>([&](auto s) FSMMC_INLINE {
                     const int rel = wave + NW * s, I = P + rel;
                     L[s] = d4{0.0, 0.0, 0.0, 0.0};
                     if (rel > t && I < R) {
@@ -309,7 +330,7 @@ __device__ double gph_loglik(const GphK& a, const double* th, double* slot, doub
                 each<4>([&](auto u) FSMMC_INLINE {
                     if (u > t && u < pc) {
                         const d4 A = tile_load(colb + u * kGphTile, lane);
-                        each<4>([&](auto s) FSMMC_INLINE {
+                        each<NS>([&](auto s) FSMMC_INLINE {
                             if (wave + NW * s >= u && P + wave + NW * s < R)
                                 acc[s][u] = tile_mac(A, L[s], acc[s][u]);
                         });
@@ -332,65 +353,91 @@ __device__ double gph_loglik(const GphK& a, const double* th, double* slot, doub
         // minus the leading columns' products: column k of the finished tiles
         // through LDS, the next one's loads in flight
         constexpr int NV = RW * kGphTile / 2 / (64 * NW);  // 16-byte units per thread
-        double2 nx[NV];
+        d2 nx[NV];
         auto fetch = [&](int k) {
-            const double2* src = reinterpret_cast<const double2*>(slot + (size_t)(k * R + base) * kGphTile);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) nx[v] = src[v * 64 * NW + threadIdx.x];
+            const d2* src = reinterpret_cast<const d2*>(slot + (size_t)(k * R + base) * kGphTile);
+            each<NV>([&](auto v) FSMMC_INLINE { nx[v] = src[v * 64 * NW + threadIdx.x]; });
         };
         fetch(0);
+#pragma unroll 1
         for (int k = 0; k < base; ++k) {
+            asm volatile("" : "+v"(lane), "+s"(wave));
             __syncthreads();  // the previous column has been read
-#pragma unroll
-            for (int v = 0; v < NV; ++v) reinterpret_cast<double2*>(colb)[v * 64 * NW + threadIdx.x] = nx[v];
+            each<NV>([&](auto v) FSMMC_INLINE { reinterpret_cast<d2*>(colb)[v * 64 * NW + threadIdx.x] = nx[v]; });
             __syncthreads();
             if (k + 1 < base) fetch(k + 1);
-            const d4 La = tile_load(colb + ra * kGphTile, lane), Lb = tile_load(colb + rb * kGphTile, lane);
+            const d4 La = tile_load(colb + wave * kGphTile, lane), Lb = tile_load(colb + (RW - 1 - wave) * kGphTile, lane);
             each<RW + 1>([&](auto p) FSMMC_INLINE {
                 const bool second = p > wave;
                 const d4 A = tile_load(colb + (second ? RW - p : p) * kGphTile, lane);
-                if (second)
-                    acc[p] = tile_mac(A, Lb, acc[p]);
-                else
-                    acc[p] = tile_mac(A, La, acc[p]);
-                __builtin_amdgcn_sched_barrier(0);
+                acc[p] = tile_mac(A, choose(second, Lb, La), acc[p]);
+                if (p % 4 == 3) __builtin_amdgcn_sched_barrier(0);
             });
         }
         __syncthreads();
     }
+    // Step t: TRSM of column t, then the updates it allows.  The owner of row
+    // t + 1 takes its tiles of column t + 1 first, factors, and leaves its other
+    // updates to the next step (column t stays in LDS: two column buffers), so
+    // the factorisation runs beside the other waves' updates (n = 414: 93.2 -> 88.2
+    // ms for 512 chains x 16 draws; with the up to four blocks per CU of the smaller
+    // classes other chains fill that time already, and n = 100 lost 2%).
+    constexpr bool kAhead = NW >= 8;
     const int nt = T - base;
+    auto owner = [](int t) { return t < NW ? t : RW - 1 - t; };
+    bool behind = false;  // this wave has not applied column t - 1 to columns past t
 #pragma unroll 1
-    for (int t = 0; t < nt; ++t) {
+    for (int t = kAhead ? -1 : 0; t < nt; ++t) {
         asm volatile("" : "+v"(lane), "+s"(wave));
         const int ra = wave, rb = RW - 1 - wave;
         const bool hasa = base + ra < R, hasb = base + rb < R;
-        if (wave == (t < NW ? t : RW - 1 - t)) {  // the owner of row t: its diagonal tile is at position w or w + 1
-            const bool last = base + t == R - 1;
-            gph_factor(pick(acc, t < NW ? wave : wave + 1), min(16, n - 16 * (base + t)), last ? yrow : -1, lane, inv, G);
-        }
-        __syncthreads();
-        const d4 iv = tile_load(inv, lane);
-        d4 La = d4{0.0, 0.0, 0.0, 0.0}, Lb = La;
-        if (ra > t && hasa) {
-            La = solve(iv, pick(acc, t), base + ra);
-            tile_store(colb + ra * kGphTile, lane, La);
-        }
-        if (rb > t && hasb) {
-            Lb = solve(iv, pick(acc, RW - t), base + rb);
-            tile_store(colb + rb * kGphTile, lane, Lb);
-        }
-        __syncthreads();
-        each<RW + 1>([&](auto p) FSMMC_INLINE {
-            const bool second = p > wave;
-            const int c = second ? RW - p : p;
-            if (c > t && base + c < T && (second ? hasb : hasa)) {
-                const d4 A = tile_load(colb + c * kGphTile, lane);
-                if (second)
-                    acc[p] = tile_mac(A, Lb, acc[p]);
-                else
-                    acc[p] = tile_mac(A, La, acc[p]);
+        auto factor = [&](int k) {
+            gph_factor(pick(acc, k < NW ? wave : wave + 1), min(16, n - 16 * (base + k)), base + k == R - 1 ? yrow : -1,
+                       lane, inv, G);
+        };
+        const bool next = kAhead && t + 1 < nt && wave == owner(t + 1);
+        if constexpr (!kAhead)
+            if (wave == owner(t)) factor(t);
+        if (!kAhead || t >= 0) {
+            double* col = colb + (t & (NB - 1)) * RW * kGphTile;
+            __syncthreads();
+            const d4 iv = tile_load(inv, lane);
+            d4 La = d4{0.0, 0.0, 0.0, 0.0}, Lb = La;
+            if (ra > t && hasa) {
+                La = solve(iv, pick(acc, t), base + ra);
+                tile_store(col + ra * kGphTile, lane, La);
             }
-        });
+            if (rb > t && hasb) {
+                Lb = solve(iv, pick(acc, RW - t), base + rb);
+                tile_store(col + rb * kGphTile, lane, Lb);
+            }
+            __syncthreads();
+            const int most = next && !behind ? t + 1 : RW;
+#pragma unroll 1
+            for (int k = behind ? t - 1 : t; k <= t; ++k) {
+                const double* ck = colb + (k & (NB - 1)) * RW * kGphTile;
+                if constexpr (kAhead) {
+                    La = tile_load(ck + ra * kGphTile, lane);
+                    Lb = tile_load(ck + rb * kGphTile, lane);
+                }
+                each<RW + 1>([&](auto p) FSMMC_INLINE {
+                    const bool second = p > wave;
+                    const int c = second ? RW - p : p;
+                    if (c > t && c <= most && base + c < T && (second ? hasb : hasa)) {
+                        const d4 A = tile_load(ck + c * kGphTile, lane);
+                        if constexpr (NW >= 8) {
+                            acc[p] = tile_mac(A, choose(second, Lb, La), acc[p]);
+                        } else if (second) {  // no registers to spare for the choice
+                            acc[p] = tile_mac(A, Lb, acc[p]);
+                        } else {
+                            acc[p] = tile_mac(A, La, acc[p]);
+                        }
+                    }
+                });
+            }
+            behind = kAhead && most == t + 1;
+        }
+        if (next) factor(t + 1);
     }
     // sums over the lanes, then over the waves in order
     double lg = log(G.pm) + (double)G.pe * 0.69314718055994530942;
@@ -560,7 +607,7 @@ __device__ __forceinline__ int gph_next_chain(unsigned long long* q, unsigned lo
 // synchronized runtime (tstop = draw + 1), recording its largest count;
 // mode 2: vmap padding of draw `draw`.
 template <int NW, bool LEAD>
-__global__ __launch_bounds__(64 * NW, NW >= 8 ? 2 : 4) void gph_kernel(GphK a, unsigned long long* q,
+__global__ __launch_bounds__(64 * NW, gph_waves_per_simd(NW)) void gph_kernel(GphK a, unsigned long long* q,
                                                                       unsigned long long base, int mode, uint32_t draw)
 {
     __shared__ __align__(16) double sm[gph_lds_doubles<NW>()];
@@ -625,7 +672,7 @@ __global__ __launch_bounds__(64 * NW, NW >= 8 ? 2 : 4) void gph_kernel(GphK a, u
 // Starting state: theta (from x0 or a prior draw N(0, I) on the INIT stream)
 // and its log-likelihood, one block per chain.
 template <int NW, bool LEAD>
-__global__ __launch_bounds__(64 * NW, NW >= 8 ? 2 : 4) void gph_init_kernel(GphK a, int has_x0)
+__global__ __launch_bounds__(64 * NW, gph_waves_per_simd(NW)) void gph_init_kernel(GphK a, int has_x0)
 {
     __shared__ __align__(16) double sm[gph_lds_doubles<NW>()];
     double* slot = LEAD ? a.slots + (size_t)blockIdx.x * a.slot_tiles * kGphTile : nullptr;
@@ -690,16 +737,19 @@ int gph_max_obs() { return kGphMaxN; }
 int gph_max_inputs() { return kGphMaxP; }
 
 // Waves per block by observations: 2 NW tile rows of 16 must hold them and y's
-// row; 8 waves are the most whose tiles fit the registers (17 tiles = 136 of
-// 256 per lane), and from 256 observations on the leading columns go through
-// memory.
-static int gph_waves(int N) { return N < 32 ? 1 : (N < 64 ? 2 : (N < 128 ? 4 : 8)); }
+// row, and the fewer waves (and tiles per wave) the more blocks a CU holds
+// (1024 chains: n = 127 with 4 waves 0.51 ms a draw, n = 128 with 6 waves 1.25,
+// with 8 waves 1.49; n = 191 1.90 with 6, 2.13 with 8).  8 waves are the most
+// whose tiles fit the registers (17 tiles = 136 of 256 per lane); from 256
+// observations on the leading columns go through memory.
+static int gph_waves(int N) { return N < 32 ? 1 : (N < 64 ? 2 : (N < 128 ? 4 : (N < 192 ? 6 : 8))); }
 
 #define FSMMC_GPH_DISPATCH(N_, CALL)    \
     switch (gph_waves(N_)) {           \
     case 1: CALL(1, false); break;     \
     case 2: CALL(2, false); break;     \
     case 4: CALL(4, false); break;     \
+    case 6: CALL(6, false); break;     \
     default:                           \
         if ((N_) < 256) {              \
             CALL(8, false);            \

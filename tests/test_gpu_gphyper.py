@@ -105,3 +105,35 @@ def test_gphyper_argument_errors(F, ctx):
     with pytest.raises(F.FsmmcError) as e:
         F.Job(ctx, target(F, w), F.ess_sampler(F.F32), 4, 4, 1)
     assert e.value.status == F.ENOTSUP
+
+
+@pytest.mark.parametrize("nobs", [15, 16, 17, 31, 32, 63, 127, 191, 192, 255, 256, 257, 271, 272, 511, 512])
+def test_gphyper_tile_edges(F, ctx, nobs):
+    # the factorisation's 16 x 16 tiles: one short of, at and past a tile; the
+    # largest of each block class (31, 63, 127, 191, 255) and the smallest of the
+    # next; leading columns through memory from 256 on (1 to 17 of them).
+    # 1e-9 as above: both sides FP64, sums in different orders
+    m, n, seed = 6, 4, 31 + nobs
+    w = inputs.gp_hyper(n=nobs, n_chains=m, seed=40 + nobs)
+    S, C, _ = run(F, ctx, w, m, n, seed, x0=w["x0"])
+    tg = O.gp_hyper_target(w["X"], w["y"], w["jitter"])
+    sp = O.ess_sampler(np.eye(3))
+    R, RC, _ = O.run_chains(tg, sp, seed, range(m), n, x0=w["x0"])
+    r = parity.check_chains(S, C, R, RC, tg, sp, seed, range(m), w["x0"], first=n, tol=1e-9)
+    assert r["worst"] <= 1e-9 and not r["bad"]
+
+
+@pytest.mark.parametrize("nobs", [5, 40, 300])
+def test_gphyper_singular_start(F, ctx, nobs):
+    # tau = 1, lambda = sigma = 0 and no jitter: C is all ones, its second pivot
+    # exactly 0, log L = -inf; the first proposal with a finite value is taken
+    m, n, seed = 4, 5, 77
+    w = inputs.gp_hyper(n=nobs, n_chains=m, seed=78)
+    x0 = np.tile(np.array([1.0, 0.0, 0.0]), (m, 1))
+    w["jitter"] = 0.0
+    S, C, _ = run(F, ctx, w, m, n, seed, x0=x0)
+    tg = O.gp_hyper_target(w["X"], w["y"], 0.0)
+    sp = O.ess_sampler(np.eye(3))
+    R, RC, _ = O.run_chains(tg, sp, seed, range(m), n, x0=x0)
+    assert np.array_equal(C, RC) and np.all(C[:, 0] == 1)
+    assert np.abs(S - R).max() <= 1e-9
