@@ -135,21 +135,21 @@ __global__ __launch_bounds__(256) void batch_fsm_kernel(const BJob* jobs_in, con
         } else if (cls <= BC_DR16) {
             const DrK& a = *(const DrK*)&jobs[item.job].dr;
             const int c = item.first + lane;
-            uint32_t steps = 0, live = 0;
+            uint32_t steps = 0, iters = 0, live = 0;
             if (c < a.m) {
                 const uint32_t stop = a.t[c] + jobs[item.job].chunk;
                 if (cls == BC_DR4)
-                    nd += dr_run<4>(a, c, stop, &steps, &live);
+                    nd += dr_run<4>(a, c, stop, &steps, &iters, &live);
                 else if (cls == BC_DR8)
-                    nd += dr_run<8>(a, c, stop, &steps, &live);
+                    nd += dr_run<8>(a, c, stop, &steps, &iters, &live);
                 else if (!WIDE || cls == BC_DR12)
-                    nd += dr_run<12>(a, c, stop, &steps, &live);
+                    nd += dr_run<12>(a, c, stop, &steps, &iters, &live);
                 else
-                    nd += dr_run<WIDE ? 16 : 12>(a, c, stop, &steps, &live);
+                    nd += dr_run<WIDE ? 16 : 12>(a, c, stop, &steps, &iters, &live);
             }
             // one atomic per wave and counter; lane occupancy as in dr_count_lanes
             const unsigned long long st = wave_sum_u64(steps), lv = wave_sum_u64(live);
-            const unsigned long long slots = 64ull * (unsigned long long)wave_max_i32((int)steps);
+            const unsigned long long slots = 64ull * (unsigned long long)wave_max_i32((int)iters);
             if (lane == 0) {
                 if (st) atomicAdd(&a.ctr[0], st);
                 if (lv) atomicAdd(&a.ctr[4], lv);

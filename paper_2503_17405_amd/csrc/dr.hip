@@ -21,18 +21,20 @@
 namespace fsmmc {
 
 // Counters are summed per wave and block: one atomic per block and counter.
-template <int NM>
+template <int D>
 __global__ __launch_bounds__(256) void dr_fsm_kernel(DrK a)
 {
+    constexpr int NM = (D + 3) / 4 * 4;
+    a.D = D;  // known here: no masks, and no normals past the dimension
     __shared__ unsigned long long s_sum;
     const int c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    uint32_t steps = 0, live = 0;
-    if (c < a.m) (void)dr_run<NM>(a, c, a.tstop, &steps, &live);
+    uint32_t steps = 0, iters = 0, live = 0;
+    if (c < a.m) (void)dr_run<NM>(a, c, a.tstop, &steps, &iters, &live);
     const unsigned long long st = block_sum_u64(wave_sum_u64(steps), &s_sum);
     if (threadIdx.x == 0 && st) atomicAdd(&a.ctr[0], st);
     const unsigned long long lv = block_sum_u64(wave_sum_u64(live), &s_sum);
     if (threadIdx.x == 0 && lv) atomicAdd(&a.ctr[4], lv);
-    dr_count_lanes(a, steps, steps, &s_sum);
+    dr_count_lanes(a, steps, iters, &s_sum);
 }
 
 template <int NM>
@@ -40,11 +42,10 @@ __device__ __forceinline__ int dr_sync_one(const DrK& a, int c, uint32_t draw, i
 {
     DrLane<NM> L;
     dr_load<NM>(a, c, L);
-    int steps = 0;
-    for (;;) {
-        const int end = dr_stage<NM>(a, c, L);
+    int steps = 0, end = 0;
+    for (int s = 0; !end; ++s) {  // the lanes still here are all at stage s
+        end = dr_stage<NM>(a, c, s, L);
         ++steps;
-        if (end) break;
     }
     *stages = L.s;
     dr_emit<NM>(a, c, L);
@@ -163,7 +164,15 @@ hipError_t dr_init_state(const JobDev& j, const void* x0, hipStream_t s)
 hipError_t dr_fsm_round(const JobDev& j, hipStream_t s)
 {
     DrK a = dr_view(j);
-    FSMMC_DR_DISPATCH(dr_fsm_kernel, j.D, dim3((j.m + 255) / 256), dim3(256), 0, s, a)
+#define FSMMC_DR_FSM(D) \
+    case D: hipLaunchKernelGGL(dr_fsm_kernel<D>, dim3((j.m + 255) / 256), dim3(256), 0, s, a); break;
+    switch (j.D) {
+        FSMMC_DR_FSM(1) FSMMC_DR_FSM(2) FSMMC_DR_FSM(3) FSMMC_DR_FSM(4) FSMMC_DR_FSM(5) FSMMC_DR_FSM(6)
+        FSMMC_DR_FSM(7) FSMMC_DR_FSM(8) FSMMC_DR_FSM(9) FSMMC_DR_FSM(10) FSMMC_DR_FSM(11) FSMMC_DR_FSM(12)
+        FSMMC_DR_FSM(13) FSMMC_DR_FSM(14) FSMMC_DR_FSM(15) FSMMC_DR_FSM(16)
+    default: return hipErrorInvalidValue;
+    }
+#undef FSMMC_DR_FSM
     return hipGetLastError();
 }
 
