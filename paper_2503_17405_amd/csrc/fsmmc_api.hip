@@ -489,18 +489,22 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         job->launches += x0 ? 2 : 3;
     } else if (d.kind == FSMMC_SLICE) {  // lane per chain, [d][chain] state
         d.Dp = d.D;
-        // direction window: W draws per chain, at most 32 and 256 MiB
-        d.W = std::max(1, std::min(32, d.n));
-        while (d.W > 1 && (double)m * d.W * d.D * 4 > 268435456.0) d.W /= 2;
-        ALLOC(d.nu, m * (size_t)d.W * d.D * 4);
+        // window of draws ahead (direction, ln u, two uniforms): the longer it is the
+        // less the wave's chains wait for each other at its end.  Up to 256 draws
+        // and 256 MiB; under an HBM budget no more than 36 D floats a chain.
+        d.W = std::max(1, std::min(256, d.n));
+        while (d.W > 1 && (double)m * d.W * (d.D + 3) * 4 > 268435456.0) d.W /= 2;
+        if (ctx->budget) {
+            int w = std::max(1, std::min(32, d.n));
+            while (w > 1 && (double)m * w * d.D * 4 > 268435456.0) w /= 2;
+            d.W = std::min(d.W, std::max(1, (w * d.D + 2 * d.D + 2) / (d.D + 3)));
+        }
+        ALLOC(d.nu, m * (size_t)d.W * (d.D + 3) * 4);
         ALLOC(d.tsnap, m * 4);
         ALLOC(d.x, m * (size_t)d.D * 4);
-        ALLOC(d.V, 2 * m * (size_t)d.D * 4);
-        ALLOC(d.logu, m * 4);
         ALLOC(d.tmin, m * 4);
         ALLOC(d.tmax, m * 4);
         ALLOC(d.theta, m * 4);
-        ALLOC(d.Wsum, m * 4);
         ALLOC(d.flags, m * 4);
         ALLOC(d.nn, m * 4);
         ALLOC(d.jd, m * 4);
