@@ -31,6 +31,8 @@ struct DrK {
     float* sink;
 };
 
+typedef const float __attribute__((address_space(4))) ConstFloat;
+
 // x / 18, correctly rounded, for x >= 0: one residual step on the product with
 // 1 / 18 gives the division's bits for every float in [2^-125, inf) (checked
 // for all of them); the rest divide.  5 instructions instead of the division's 12.
@@ -52,9 +54,13 @@ __device__ __forceinline__ float dr_logpdf(const DrK& a, const float* v)
         const float u = v[0];
         return -div18(u * u) - 0.5f * (float)(a.D - 1) * u - 0.5f * expf(-u) * ss;
     }
+    // through the constant address space: nothing writes the precisions while a
+    // kernel runs, so they are read once, not in every density (a load there
+    // waits for the draws' stores as well)
+    const ConstFloat* prec = (const ConstFloat*)a.prec;
     float s = 0.0f;
 #pragma unroll
-    for (int d = 0; d < NM; ++d) s += (d < a.D ? a.prec[d] : 0.0f) * v[d] * v[d];
+    for (int d = 0; d < NM; ++d) s += (d < a.D ? prec[d] : 0.0f) * v[d] * v[d];
     return -0.5f * s;
 }
 
