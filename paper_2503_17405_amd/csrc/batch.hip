@@ -12,7 +12,7 @@
 //      FSM steps with the same device functions as the single-job kernels;
 //   4. nuts_steps NUTS runtime steps for every NUTS job: grouped transition
 //      (one wavefront per chain; it adds up the row-slice partials of the
-//      gradient it consumes), per-job request compaction and grouped
+//      gradient it consumes), per-job request lists and grouped
 //      logistic-regression gradient tiles;
 //   5. batch_tally_kernel: per job, chains short of n and draws so far.
 // Every random number is keyed by (seed, chain, draw, role, sub) and every
@@ -46,8 +46,6 @@ struct BJob {
     uint32_t chunk;  // DRMH draws per chain per round
     int32_t m, n;
     const uint32_t* t;  // chain draw counters
-    int32_t* list;      // NUTS request list and count
-    int32_t* count;
     unsigned long long* ctr;
     EssK<float> ess;
     NuK<float> nu;
@@ -57,7 +55,7 @@ struct BJob {
 };
 
 struct BItem {
-    int32_t job, first;  // ESS: chain; DRMH: first of 64 chains; NUTS: chain / first of 4
+    int32_t job, first;  // ESS: chain; DRMH: first of 64 chains; NUTS: first of 4 chains
 };
 
 struct BTile {
@@ -84,11 +82,15 @@ struct BJobStat {
 // in registers across a chain's loop.
 typedef const BJob __attribute__((address_space(4))) ConstBJob;
 
-__global__ void batch_begin_kernel(BHdr* h)
+// Also clears the request counts (slot 0) of the round's first NUTS step.
+__global__ __launch_bounds__(256) void batch_begin_kernel(BHdr* h, const BJob* jobs, const int32_t* njobs, int n_nuts)
 {
-    h->next = 0;
-    h->live = 0;
-    h->fsm_draws = 0;
+    if (threadIdx.x == 0) {
+        h->next = 0;
+        h->live = 0;
+        h->fsm_draws = 0;
+    }
+    for (int i = threadIdx.x; i < n_nuts; i += blockDim.x) jobs[njobs[i]].nuts.rcnt[0] = 0u;
 }
 
 template <int RT, int CT>
@@ -161,28 +163,26 @@ __global__ __launch_bounds__(256) void batch_fsm_kernel(const BJob* jobs_in, con
     if (nd) atomicAdd(&h->fsm_draws, nd);
 }
 
-// NUTS: one wavefront per chain of the item table.
-template <int EPL>
-__global__ __launch_bounds__(256) void batch_nuts_step_kernel(const BJob* jobs_in, const BItem* items, int n)
+// NUTS: one wavefront per chain; a block takes four chains of one job (the item
+// names the first).  Requests go to the job's list, slot `slot`; the other of
+// slots 0 and 1, which the next step uses, is cleared.
+template <int EPL, bool AHEAD>
+__global__ __launch_bounds__(256) void batch_nuts_step_kernel(const BJob* jobs_in, const BItem* items, int slot)
 {
     const ConstBJob* jobs = (const ConstBJob*)jobs_in;
-    const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
-    if (w >= n) return;
-    BItem it = items[w];
+    BItem it = items[blockIdx.x];
     it.job = __builtin_amdgcn_readfirstlane(it.job);
     it.first = __builtin_amdgcn_readfirstlane(it.first);
     const NutsK& a = *(const NutsK*)&jobs[it.job].nuts;
-    nuts_chain_step<EPL>(a, it.first, threadIdx.x & 63);
-}
-
-__global__ __launch_bounds__(1024) void batch_nuts_compact_kernel(const BJob* jobs, const int32_t* njobs)
-{
-    const BJob& J = jobs[njobs[blockIdx.x]];
-    nuts_compact_block<1024>(J.nuts.req, J.m, 0, J.list, J.count, J.ctr);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), c = it.first + wave;
+    if (it.first == 0 && threadIdx.x == 0) a.rcnt[slot ^ 1] = 0u;
+    int bits = 0;
+    if (c < a.m) bits = nuts_chain_step<EPL, AHEAD>(a, c, threadIdx.x & 63);
+    nuts_append<4>(a, c, wave, bits, slot);
 }
 
 template <int DT>
-__global__ __launch_bounds__(512) void batch_grad_kernel(const BJob* jobs_in, const BGrad* tiles)
+__global__ __launch_bounds__(512) void batch_grad_kernel(const BJob* jobs_in, const BGrad* tiles, int slot)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     const ConstBJob* jobs = (const ConstBJob*)jobs_in;
@@ -191,16 +191,16 @@ __global__ __launch_bounds__(512) void batch_grad_kernel(const BJob* jobs_in, co
     // the job's dimension class fixed at compile time, as in the single-job
     // kernel (a runtime class leaves the tile's per-k arrays in scratch)
 #define FSMMC_TILE_CASE(K) \
-    case K: logreg_grad_tile<DT, (K)>(a, t.ct, t.sl, lds); break;
+    case K: logreg_grad_tile<DT, (K)>(a, t.ct, t.sl, lds, slot); break;
     if constexpr (DT == 2) {
         switch ((a.D + 7) >> 3) {
             FSMMC_TILE_CASE(1) FSMMC_TILE_CASE(2) FSMMC_TILE_CASE(3) FSMMC_TILE_CASE(4)
-            FSMMC_TILE_CASE(5) FSMMC_TILE_CASE(6) FSMMC_TILE_CASE(7) default: logreg_grad_tile<DT, 8>(a, t.ct, t.sl, lds);
+            FSMMC_TILE_CASE(5) FSMMC_TILE_CASE(6) FSMMC_TILE_CASE(7) default: logreg_grad_tile<DT, 8>(a, t.ct, t.sl, lds, slot);
         }
     } else {
         switch ((a.D + 7) >> 3) {
             FSMMC_TILE_CASE(9) FSMMC_TILE_CASE(10) FSMMC_TILE_CASE(11) FSMMC_TILE_CASE(12)
-            FSMMC_TILE_CASE(13) FSMMC_TILE_CASE(14) FSMMC_TILE_CASE(15) default: logreg_grad_tile<DT, 16>(a, t.ct, t.sl, lds);
+            FSMMC_TILE_CASE(13) FSMMC_TILE_CASE(14) FSMMC_TILE_CASE(15) default: logreg_grad_tile<DT, 16>(a, t.ct, t.sl, lds, slot);
         }
     }
 #undef FSMMC_TILE_CASE
@@ -272,6 +272,17 @@ hipError_t launch_tiles(int slot, int ntiles, const BJob* jobs, const BTile* til
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+// nblocks: items of four chains.  Vectors ahead of the step while the blocks
+// leave CUs idle (512 chains; the single-job rule in nuts.hip has the figures).
+template <int EPL>
+void launch_nuts_steps(int nblocks, const BJob* jobs, const BItem* items, int slot, hipStream_t s)
+{
+    if (nblocks <= 128)
+        hipLaunchKernelGGL((batch_nuts_step_kernel<EPL, true>), dim3(nblocks), dim3(256), 0, s, jobs, items, slot);
+    else
+        hipLaunchKernelGGL((batch_nuts_step_kernel<EPL, false>), dim3(nblocks), dim3(256), 0, s, jobs, items, slot);
 }
 
 int kind_slot(int kind) { return kind == FSMMC_ESS ? 0 : (kind == FSMMC_DRMH ? 1 : 2); }
@@ -374,12 +385,11 @@ fsmmc_status rebuild(fsmmc_batch* b)
         } else {
             J.nuts = nuts_view(d, 0, 0);
             J.grad = grad_view(d, 0);
-            J.list = d.list;
-            J.count = d.count;
+            J.grad.count = (const int32_t*)(d.wctr + 6);  // the step kernels' slots
             if (!on) continue;
             J.cls = BC_NUTS;
             const int e = d.EPL == 1 ? 0 : 1;
-            for (int c = 0; c < d.m; ++c) nsteps[e].push_back(BItem{i, c});
+            for (int c = 0; c < d.m; c += 4) nsteps[e].push_back(BItem{i, c});
             for (int ct = 0; ct * 128 < d.m; ++ct)
                 for (int sl = 0; sl < d.nslices; ++sl) grads[e].push_back(BGrad{i, ct, sl, 0});
             njobs.push_back(i);
@@ -435,7 +445,7 @@ fsmmc_status rebuild(fsmmc_batch* b)
     auto chk = [&]() {
         if (e == hipSuccess) e = hipGetLastError();
     };
-    hipLaunchKernelGGL(batch_begin_kernel, dim3(1), dim3(1), 0, s, h);
+    hipLaunchKernelGGL(batch_begin_kernel, dim3(1), dim3(256), 0, s, h, jobs, (const int32_t*)b->d_njobs, b->n_nuts);
     chk();
     for (int t = 0; t < kTileSlots && e == hipSuccess; ++t)
         if (b->tile_cnt[t] > 0) e = launch_tiles(t, b->tile_cnt[t], jobs, b->d_tiles + b->tile_off[t], s);
@@ -451,22 +461,18 @@ fsmmc_status rebuild(fsmmc_batch* b)
     for (int step = 0; step < b->nuts_steps && b->n_nuts > 0 && e == hipSuccess; ++step) {
         const BItem* st1 = b->d_nitems;
         const BItem* st2 = st1 + b->nstep_cnt[0];
+        const int slot = step & 1;
         if (b->nstep_cnt[0])
-            hipLaunchKernelGGL(batch_nuts_step_kernel<1>, dim3((b->nstep_cnt[0] + 3) / 4), dim3(256), 0, s, jobs,
-                               st1, b->nstep_cnt[0]);
+            launch_nuts_steps<1>(b->nstep_cnt[0], jobs, st1, slot, s);
         if (b->nstep_cnt[1])
-            hipLaunchKernelGGL(batch_nuts_step_kernel<2>, dim3((b->nstep_cnt[1] + 3) / 4), dim3(256), 0, s, jobs,
-                               st2, b->nstep_cnt[1]);
-        chk();
-        hipLaunchKernelGGL(batch_nuts_compact_kernel, dim3(b->n_nuts), dim3(1024), 0, s, jobs,
-                           (const int32_t*)b->d_njobs);
+            launch_nuts_steps<2>(b->nstep_cnt[1], jobs, st2, slot, s);
         chk();
         if (b->grad_cnt[0])
             hipLaunchKernelGGL(batch_grad_kernel<2>, dim3(b->grad_cnt[0]), dim3(512), GradB<2>::LDS, s, jobs,
-                               (const BGrad*)b->d_grads);
+                               (const BGrad*)b->d_grads, slot);
         if (b->grad_cnt[1])
             hipLaunchKernelGGL(batch_grad_kernel<4>, dim3(b->grad_cnt[1]), dim3(512), GradB<4>::LDS, s, jobs,
-                               (const BGrad*)b->d_grads + b->grad_cnt[0]);
+                               (const BGrad*)b->d_grads + b->grad_cnt[0], slot);
         chk();
     }
     if (e == hipSuccess && nj > 0) {

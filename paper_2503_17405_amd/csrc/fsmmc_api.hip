@@ -669,7 +669,7 @@ static fsmmc_status progress(fsmmc_job* job, std::vector<uint32_t>& t, std::vect
     return FSMMC_OK;
 }
 
-// NUTS runtime: steps of {transition, compaction, gradient, reduce}, issued in
+// NUTS runtime: steps of {transition (and request list), gradient}, issued in
 // batches; after each batch the host reads how many chains are still alive
 // and how many asked for a gradient in the last step.
 static fsmmc_status nuts_run(fsmmc_job* job, int mode, int64_t max_steps, uint32_t tstop, int32_t* all_done)
@@ -679,6 +679,7 @@ static fsmmc_status nuts_run(fsmmc_job* job, int mode, int64_t max_steps, uint32
     const int64_t b = max_steps > 0 ? max_steps : INT64_MAX;
     hipLaunchKernelGGL(fill_i64_kernel, dim3((d.m + 255) / 256), dim3(256), 0, job->stream, d.budget, b, d.m);
     HIP_TRY(hipGetLastError());
+    if (mode == 0) HIP_TRY(fill_i32((int32_t*)d.wctr + 6, 0, 3, job->stream));
     job->launches++;
     const int batch = 16;
     uint32_t* h = reinterpret_cast<uint32_t*>(job->h_ctr + 8);
@@ -687,18 +688,16 @@ static fsmmc_status nuts_run(fsmmc_job* job, int mode, int64_t max_steps, uint32
         for (int i = 0; i < batch; ++i) {
             const uint32_t s = job->step;
             HIP_TRY(launch(job, mode == 0 ? KC_FSM : KC_SYNC, [&] { return nuts_transition(d, mode, s, job->stream); }));
-            HIP_TRY(launch(job, KC_G, [&] { return nuts_gradient(d, job->stream); }));
+            HIP_TRY(launch(job, KC_G, [&] { return nuts_gradient(d, mode, s, job->stream); }));
             job->step++;
         }
-        HIP_TRY(hipMemcpyAsync(h, d.wctr, 6 * 4, hipMemcpyDeviceToHost, job->stream));
-        HIP_TRY(hipMemcpyAsync(h + 6, d.count, 4, hipMemcpyDeviceToHost, job->stream));
+        HIP_TRY(hipMemcpyAsync(h, d.wctr, 9 * 4, hipMemcpyDeviceToHost, job->stream));
         HIP_TRY(hipStreamSynchronize(job->stream));
         harvest(job);
-        const uint32_t reqs = h[6];
         if (mode == 0) {
             // FSM: a chain short of tstop requests a gradient every step unless its
             // budget is spent, so no request means every chain is done or out of budget
-            if (reqs == 0) break;
+            if (h[6 + (job->step - 1) % 3] == 0) break;
             continue;
         }
         alive = h[3 + (job->step - 1) % 3];
@@ -955,10 +954,11 @@ fsmmc_status fsmmc_step_fsm_async(fsmmc_job* job, int64_t max_steps, int32_t* do
     HIP_TRY(fill_i64(d.budget, b, d.m, s));
     job->launches++;
     if (nuts_lr) {
+        HIP_TRY(fill_i32((int32_t*)d.wctr + 6, 0, 3, s));
         for (int64_t i = 0; i <= max_steps; ++i) {
             const uint32_t st = job->step;
             HIP_TRY(launch(job, KC_FSM, [&] { return nuts_transition(d, 0, st, s); }));
-            HIP_TRY(launch(job, KC_G, [&] { return nuts_gradient(d, s); }));
+            HIP_TRY(launch(job, KC_G, [&] { return nuts_gradient(d, 0, st, s); }));
             job->step++;
         }
     } else if (d.kind == FSMMC_NUTS) {  // mixture: one persistent launch

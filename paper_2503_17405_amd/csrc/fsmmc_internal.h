@@ -75,7 +75,7 @@ struct JobDev {
     int32_t* count = nullptr;  // 1
     void* Gpart = nullptr;     // nslices x m x Dp
     void* Upart = nullptr;     // nslices x m
-    uint32_t* wctr = nullptr;  // [0..2] chains still in their draw, [3..5] chains alive (per step mod 3)
+    uint32_t* wctr = nullptr;  // [0..2] chains still in their draw, [3..5] chains alive, [6..8] FSM requests (per step mod 3)
     int slice_rows = 0, nslices = 0;
     uint32_t tstop = 0;        // chains stop at this draw count
     void* acc = nullptr;       // m: sum over leapfrogs of min(1, e^(H0 - H)) (FP32)
@@ -112,7 +112,7 @@ int ess_supported_epl(int D, int dtype);
 int nuts_nvec(int max_depth);
 hipError_t nuts_init_state(const JobDev& j, const void* x0, hipStream_t s);
 hipError_t nuts_transition(const JobDev& j, int mode, uint32_t step, hipStream_t s);
-hipError_t nuts_gradient(const JobDev& j, hipStream_t s);
+hipError_t nuts_gradient(const JobDev& j, int mode, uint32_t step, hipStream_t s);  // after nuts_transition(mode, step)
 size_t logreg_split_bytes(const JobDev& j);
 hipError_t logreg_setup(const JobDev& j, hipStream_t s);
 hipError_t nuts_gradient_dense(const JobDev& j, int ncols, float* Gout, float* Uout, int gstride, hipStream_t s);

@@ -88,12 +88,11 @@ static hipError_t grad_dispatch(const JobDev& j, const GradK& g, hipStream_t s, 
 #undef FSMMC_GRAD_CASE
 }
 
-// Gout == nullptr: leave the row-slice partials for the consumer to add.
 static hipError_t grad_launch(const JobDev& j, int dense, float* Gout, float* Uout, int gstride, hipStream_t s)
 {
     const GradK g = grad_view(j, dense);
     hipError_t e = grad_dispatch(j, g, s, false);
-    if (e != hipSuccess || !Gout) return e;
+    if (e != hipSuccess) return e;
     const ReduceK r = reduce_view(j, dense, Gout, Uout, gstride);
     const dim3 rg((j.m + 3) / 4);
     if (j.Dp <= 64)
@@ -122,9 +121,11 @@ hipError_t logreg_setup(const JobDev& j, hipStream_t s)
     return grad_dispatch(j, grad_view(j, 0), s, true);
 }
 
-hipError_t nuts_gradient(const JobDev& j, hipStream_t s)
+hipError_t nuts_gradient(const JobDev& j, int mode, uint32_t step, hipStream_t s)
 {
-    return grad_launch(j, 0, nullptr, nullptr, 0, s);
+    GradK g = grad_view(j, 0);
+    if (mode == 0) g.count = (const int32_t*)(j.wctr + 6 + step % 3);  // the step kernel's slot
+    return grad_dispatch(j, g, s, false);
 }
 
 hipError_t nuts_gradient_dense(const JobDev& j, int ncols, float* Gout, float* Uout, int gstride, hipStream_t s)

@@ -19,7 +19,7 @@ struct GradK {
     const float* y;   // Np
     const float* Th;  // m x Dp, indexed by chain
     const int32_t* list;
-    const int32_t* count;
+    const int32_t* count;  // columns in the list (at the slot the tile is given)
     float* Gpart;  // nslices x m x Dp (indexed by chain)
     float* Upart;  // nslices x m
 };
@@ -95,7 +95,7 @@ __device__ __forceinline__ floatx4 mfma_bf16x6(const uint4 (&A)[3], const uint4 
 // c + 1 (X waves) are loaded into registers at the top of the pass and
 // written to the idle LDS buffers at its end.
 template <int DT, int NK8 = 0>
-__device__ __forceinline__ void logreg_grad_tile(const GradK& a, int ct, int sl, unsigned char* lds)
+__device__ __forceinline__ void logreg_grad_tile(const GradK& a, int ct, int sl, unsigned char* lds, int slot = 0)
 {
     using S = GradB<DT>;
     constexpr int DP = S::DP, PR = S::PR;
@@ -108,7 +108,7 @@ __device__ __forceinline__ void logreg_grad_tile(const GradK& a, int ct, int sl,
     float* Ured = reinterpret_cast<float*>(lds + S::AUX0);  // [E wave][2 chain tiles][16]
     int* cols = reinterpret_cast<int*>(Ured + 8 * 32);
 
-    const int ncols = a.dense > 0 ? a.dense : *a.count;
+    const int ncols = a.dense > 0 ? a.dense : a.count[slot];
     if (ct * 128 >= ncols) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, q4 = lane >> 4;

@@ -179,11 +179,13 @@ __global__ __launch_bounds__(512) void nuts_mog_kernel(NutsK a, MogK mk, unsigne
         const uint32_t t = uni(a.t[c]);
         if (t >= a.tstop) continue;
         NutsScal S = nuts_load(a, c, t);
+        NutsBox<EPL, BOX_HELD> box(a.V + (size_t)c * a.nvec * a.Dp, a.Dp, lane);
         int bits;
         do {
-            bits = nuts_chain_body<EPL>(a, G, c, lane, S);
+            bits = nuts_chain_body<EPL, MogGrad, false, BOX_HELD>(a, G, c, lane, S, box);
             steps += (bits & NC_REQ) ? 1ull : 0ull;
         } while (bits & NC_REQ);
+        box.write_back();
         nuts_store(a, c, S, 0, lane);
         if (sync && lane == 0 && S.t > t) atomicMax(&a.maxN[t], S.nleap);
     }

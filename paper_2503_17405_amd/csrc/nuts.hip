@@ -4,29 +4,47 @@
 // and an inner integration loop), for Bayesian logistic regression.
 //
 // One runtime step for every chain:
-//   1. nuts_step_kernel (one wavefront per chain): add up the row-slice
+//   1. nuts_fsm_step_kernel (one wavefront per chain): add up the row-slice
 //      partials of the gradient that just arrived, in slice order
 //      (grad U = theta - X^T r, U = |theta|^2 / 2 - loglik), finish that
 //      leapfrog (second half-kick, multinomial leaf choice, U-turn
 //      checkpoints), then run the cheap states back to back (CHECK, DONE,
 //      INIT, DOUBLE) until the chain needs the next gradient, and issue the
 //      first half of that leapfrog (Appendix, Alg. "bundled step as input to
-//      amortized step").
-//   2. nuts_compact_kernel: list of chains that asked for a gradient, in
-//      chain order.
-//   3. logreg_grad_bf16_kernel: eta = X Theta, r = y - sigmoid(eta), X^T r
+//      amortized step").  Each block appends its requesters to the step's list.
+//   2. logreg_grad_bf16_kernel: eta = X Theta, r = y - sigmoid(eta), X^T r
 //      and the log-likelihood, fused for a tile of 128 listed chains and a
 //      slice of rows on the bf16 matrix cores (exact three-piece splits of
 //      the FP32 operands, FP32 results); eta never leaves registers.
-// The synchronized runtime uses the same kernels; a chain that finishes a
-// draw waits until every chain has finished it (device-side barrier), and in
-// vmap mode the gradient phase then covers every chain.
+// The synchronized runtime runs the same step (nuts_step_kernel) and lists its
+// requesters in chain order with a kernel of their own (nuts_compact_kernel); a
+// chain that finishes a draw waits until every chain has finished it
+// (device-side barrier), and in vmap mode the gradient phase then covers every
+// chain.
 // Readings: multinomial leaf sampling inside a subtree, biased progressive
 // merge of subtrees, generalized U-turn criterion on every aligned sub-span,
 // divergence when H - H0 > 1000, identity mass.
 #include "nuts_device.h"
 
 namespace fsmmc {
+
+// FSM runtime: NW chains per block, their requests appended to the list (slot
+// step mod 3; the next step's slot is cleared here).  Bound by latency at few
+// chains (one round trip for the state, then a serial chain of vector work) and
+// by the state's bytes at many.  A list built by a kernel of its own cost 2.1 us
+// and a launch gap per step at 16 chains, 5.2 us at 4096: 16 chains (N = 1000,
+// D = 10, 200 draws, depth 10) 31.6 -> 27.8 ms, 4096 chains (N = 10^4, D = 100)
+// 4.5% faster.
+template <int EPL, int NW, bool AHEAD>
+__global__ __launch_bounds__(64 * NW) void nuts_fsm_step_kernel(NutsK a)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = (int)(blockIdx.x * NW) + wave;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.rcnt[(a.step + 1) % 3] = 0u;
+    int bits = 0;
+    if (c < a.m) bits = nuts_chain_step<EPL, AHEAD>(a, c, lane);
+    nuts_append<NW>(a, c, wave, bits, (int)(a.step % 3));
+}
 
 template <int EPL>
 __global__ __launch_bounds__(256) void nuts_step_kernel(NutsK a)
@@ -38,24 +56,22 @@ __global__ __launch_bounds__(256) void nuts_step_kernel(NutsK a)
         a.wctr[3 + (a.step + 1) % 3] = 0u;
     }
     int bits = 0;
-    if (c < a.m) bits = nuts_chain_step<EPL>(a, c, lane);
-    if (a.mode != 0) {
-        // synchronized runtimes: chains alive / still inside their draw, one atomic per block
-        __shared__ unsigned s_alive, s_indraw;
-        if (threadIdx.x == 0) {
-            s_alive = 0;
-            s_indraw = 0;
-        }
-        __syncthreads();
-        if (lane == 0 && bits) {
-            atomicAdd(&s_alive, (bits & NC_ALIVE) ? 1u : 0u);
-            atomicAdd(&s_indraw, (bits & NC_INDRAW) ? 1u : 0u);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            if (s_alive) atomicAdd(&a.wctr[3 + a.step % 3], s_alive);
-            if (s_indraw) atomicAdd(&a.wctr[a.step % 3], s_indraw);
-        }
+    if (c < a.m) bits = nuts_chain_step<EPL>(a, SliceGrad{a}, c, lane);
+    // chains alive / still inside their draw, one atomic per block
+    __shared__ unsigned s_alive, s_indraw;
+    if (threadIdx.x == 0) {
+        s_alive = 0;
+        s_indraw = 0;
+    }
+    __syncthreads();
+    if (lane == 0 && bits) {
+        atomicAdd(&s_alive, (bits & NC_ALIVE) ? 1u : 0u);
+        atomicAdd(&s_indraw, (bits & NC_INDRAW) ? 1u : 0u);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (s_alive) atomicAdd(&a.wctr[3 + a.step % 3], s_alive);
+        if (s_indraw) atomicAdd(&a.wctr[a.step % 3], s_indraw);
     }
 }
 
@@ -102,9 +118,38 @@ hipError_t nuts_init_state(const JobDev& j, const void* x0, hipStream_t s)
     return nuts_gradient_dense(j, j.m, gp, (float*)j.lx, vstride, s);
 }
 
+template <int EPL, int NW, bool AHEAD>
+static void fsm_step_launch(const NutsK& a, hipStream_t s)
+{
+    hipLaunchKernelGGL((nuts_fsm_step_kernel<EPL, NW, AHEAD>), dim3((a.m + NW - 1) / NW), dim3(64 * NW), 0, s, a);
+}
+
+// Four chains per block up to 1024 chains (every block has a CU to itself),
+// eight above, where the blocks' atomics on the one count cost more than the
+// wait for a block's slowest chain.  Vectors ahead up to 2048 chains: D = 20, 16
+// chains, 100 draws 33.0 -> 24.6 ms; D = 20, 2048 chains, 25 draws 10.4 -> 9.5;
+// at 65536 chains the extra reads cost 16.0 -> 16.6, at D = 100 42.2 -> 50.2.
+template <int EPL>
+static void fsm_step(const NutsK& a, hipStream_t s)
+{
+    if (a.m <= 1024)
+        fsm_step_launch<EPL, 4, true>(a, s);
+    else if (a.m <= 2048)
+        fsm_step_launch<EPL, 8, true>(a, s);
+    else
+        fsm_step_launch<EPL, 8, false>(a, s);
+}
+
 hipError_t nuts_transition(const JobDev& j, int mode, uint32_t step, hipStream_t s)
 {
     NutsK a = nuts_view(j, mode, step);
+    if (mode == 0) {
+        if (j.Dp <= 64)
+            fsm_step<1>(a, s);
+        else
+            fsm_step<2>(a, s);
+        return hipGetLastError();
+    }
     const dim3 grid((j.m + 3) / 4), block(256);
     if (j.Dp <= 64)
         hipLaunchKernelGGL(nuts_step_kernel<1>, grid, block, 0, s, a);

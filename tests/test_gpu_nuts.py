@@ -198,3 +198,18 @@ def test_nuts_full_size_fsm_equals_synchronized(F, ctx):
     assert np.array_equal(Ca, Cb)
     assert torch.isfinite(a).all()
     print("full size: mean leapfrogs %.2f, max %d, steps %d" % (Ca.mean(), Ca.max(), sa["steps"]))
+
+
+@pytest.mark.parametrize("m", [1, 7, 1024, 1025, 2047, 2051])
+@pytest.mark.parametrize("D", [3, 70])
+def test_nuts_request_lists_at_block_edges(F, ctx, m, D):
+    """The FSM step's chain blocks (4 or 8 chains) and their appended request
+    lists, against the synchronized runtime's list in chain order: same bits,
+    whole and in pieces of 5 gradients, with partly filled last blocks."""
+    d = inputs.logreg(n_data=64, dim=D, seed=3)
+    S, C, st = gpu_nuts(F, ctx, d, m, 6, 11, 0.2, 4)
+    S1, C1, st1 = gpu_nuts(F, ctx, d, m, 6, 11, 0.2, 4, max_steps=5)
+    S2, C2, _ = gpu_nuts(F, ctx, d, m, 6, 11, 0.2, 4, runtime="compact")
+    assert np.array_equal(C, C2) and np.array_equal(S, S2)
+    assert np.array_equal(C, C1) and np.array_equal(S, S1)
+    assert st["steps"] == st1["steps"] == int(C.sum())
