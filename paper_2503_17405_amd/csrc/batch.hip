@@ -13,7 +13,9 @@
 //   4. nuts_steps NUTS runtime steps for every NUTS job: grouped transition
 //      (one wavefront per chain; it adds up the row-slice partials of the
 //      gradient it consumes), per-job request lists and grouped
-//      logistic-regression gradient tiles;
+//      logistic-regression gradient tiles; jobs whose gradient one compute
+//      unit goes through quickly run all nuts_steps in one launch instead, in
+//      blocks that hold their chains (nuts_block.h);
 //   5. batch_tally_kernel: per job, chains short of n and draws so far.
 // Every random number is keyed by (seed, chain, draw, role, sub) and every
 // reduction has a fixed order, so a job's draws do not depend on the batch,
@@ -32,7 +34,7 @@
 #include "ess_device.h"
 #include "logreg_device.h"
 #include "multi.h"
-#include "nuts_device.h"
+#include "nuts_block.h"
 
 namespace fsmmc {
 
@@ -52,6 +54,7 @@ struct BJob {
     DrK dr;
     NutsK nuts;
     GradK grad;
+    int32_t nblock;  // NUTS: chains per block of the block kernel, 0: a launch per step
 };
 
 struct BItem {
@@ -179,6 +182,25 @@ __global__ __launch_bounds__(256) void batch_nuts_step_kernel(const BJob* jobs_i
     int bits = 0;
     if (c < a.m) bits = nuts_chain_step<EPL, AHEAD>(a, c, threadIdx.x & 63);
     nuts_append<4>(a, c, wave, bits, slot);
+}
+
+// NUTS jobs whose blocks compute their own gradients: K steps (item: the block's
+// first chain).
+__global__ __launch_bounds__(64 * kNutsBlockWaves) void batch_nuts_block_kernel(const BJob* jobs_in, const BItem* items,
+                                                                                int K)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    const ConstBJob* jobs = (const ConstBJob*)jobs_in;
+    BItem it = items[blockIdx.x];
+    it.job = __builtin_amdgcn_readfirstlane(it.job);
+    it.first = __builtin_amdgcn_readfirstlane(it.first);
+    const BJob& J = *(const BJob*)&jobs[it.job];
+    switch (nuts_block_class(J.nuts.D)) {
+    case 1: nuts_block_run<1, 1, 0>(J.nuts, J.grad, it.first, J.nblock, K, lds, nullptr); break;
+    case 2: nuts_block_run<1, 2, 0>(J.nuts, J.grad, it.first, J.nblock, K, lds, nullptr); break;
+    case 3: nuts_block_run<2, 3, 0>(J.nuts, J.grad, it.first, J.nblock, K, lds, nullptr); break;
+    default: nuts_block_run<2, 4, 0>(J.nuts, J.grad, it.first, J.nblock, K, lds, nullptr);
+    }
 }
 
 template <int DT>
@@ -350,6 +372,11 @@ fsmmc_status rebuild(fsmmc_batch* b)
     std::vector<BItem> nsteps[2];
     std::vector<BGrad> grads[2];
     std::vector<int32_t> njobs;
+    std::vector<std::pair<double, BItem>> nblocks;
+    b->nblock_lds = 0;
+    int64_t nuts_chains = 0;  // that compete for the compute units
+    for (int i = 0; i < nj; ++i)
+        if (b->jobs[i]->d.kind == FSMMC_NUTS && b->live[i] && (b->mask & MASK_NUTS)) nuts_chains += b->jobs[i]->d.m;
     for (int i = 0; i < nj; ++i) {
         JobDev& d = b->jobs[i]->d;
         BJob& J = jv[i];
@@ -388,6 +415,13 @@ fsmmc_status rebuild(fsmmc_batch* b)
             J.grad.count = (const int32_t*)(d.wctr + 6);  // the step kernels' slots
             if (!on) continue;
             J.cls = BC_NUTS;
+            J.nblock = nuts_block_chains(d, nuts_chains);
+            if (J.nblock) {
+                const int nt = nuts_block_class(d.D);
+                b->nblock_lds = std::max(b->nblock_lds, nuts_block_lds(J.nblock, d.nslices, nt, d.max_depth).bytes);
+                for (int c = 0; c < d.m; c += J.nblock) nblocks.push_back({(double)d.N * nt, BItem{i, c}});
+                continue;
+            }
             const int e = d.EPL == 1 ? 0 : 1;
             for (int c = 0; c < d.m; c += 4) nsteps[e].push_back(BItem{i, c});
             for (int ct = 0; ct * 128 < d.m; ++ct)
@@ -395,10 +429,11 @@ fsmmc_status rebuild(fsmmc_batch* b)
             njobs.push_back(i);
         }
     }
-    std::stable_sort(items.begin(), items.end(),
-                     [](const std::pair<double, BItem>& x, const std::pair<double, BItem>& y) {
-                         return x.first > y.first;
-                     });
+    const auto longer = [](const std::pair<double, BItem>& x, const std::pair<double, BItem>& y) {
+        return x.first > y.first;
+    };
+    std::stable_sort(items.begin(), items.end(), longer);
+    std::stable_sort(nblocks.begin(), nblocks.end(), longer);
     std::vector<BItem> iv(items.size());
     for (size_t k = 0; k < items.size(); ++k) iv[k] = items[k].second;
     std::vector<BTile> tv;
@@ -412,6 +447,8 @@ fsmmc_status rebuild(fsmmc_batch* b)
         b->nstep_cnt[e] = (int)nsteps[e].size();
         nv.insert(nv.end(), nsteps[e].begin(), nsteps[e].end());
     }
+    b->nblock_cnt = (int)nblocks.size();
+    for (const auto& x : nblocks) nv.push_back(x.second);
     std::vector<BGrad> gv;
     for (int e = 0; e < 2; ++e) {
         b->grad_cnt[e] = (int)grads[e].size();
@@ -456,6 +493,11 @@ fsmmc_status rebuild(fsmmc_batch* b)
         else
             hipLaunchKernelGGL(batch_fsm_kernel<false>, dim3(b->fsm_blocks), dim3(256), 0, s, jobs,
                                (const BItem*)b->d_items, b->n_items, h);
+        chk();
+    }
+    if (e == hipSuccess && b->nblock_cnt > 0 && b->nuts_steps > 0) {
+        hipLaunchKernelGGL(batch_nuts_block_kernel, dim3(b->nblock_cnt), dim3(64 * kNutsBlockWaves), b->nblock_lds, s,
+                           jobs, (const BItem*)b->d_nitems + b->nstep_cnt[0] + b->nstep_cnt[1], b->nuts_steps);
         chk();
     }
     for (int step = 0; step < b->nuts_steps && b->n_nuts > 0 && e == hipSuccess; ++step) {
@@ -538,6 +580,8 @@ fsmmc_status batch_setup(fsmmc_batch* b, fsmmc_ctx* ctx, void* stream, const fsm
     }
     HIP_TRY(hipEventCreate(&b->e0));
     HIP_TRY(hipEventCreate(&b->e1));
+    HIP_TRY(hipFuncSetAttribute((const void*)batch_nuts_block_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kNutsBlockLds));
     HIP_TRY(hipFuncSetAttribute((const void*)batch_grad_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 GradB<2>::LDS));
     HIP_TRY(hipFuncSetAttribute((const void*)batch_grad_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -639,6 +639,7 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
                                      hipMemcpyDeviceToDevice, job->stream));
         HIP_TRY_JOB(hipMemcpyAsync(d.y, target->y, (size_t)d.N * 4, hipMemcpyDeviceToDevice, job->stream));
         HIP_TRY_JOB(logreg_setup(d, job->stream));
+        if (nuts_block_chains(d, d.m)) HIP_TRY_JOB(nuts_block_setup(d));
         hipLaunchKernelGGL(fill_i32_kernel, dim3((d.m + 255) / 256), dim3(256), 0, job->stream, d.k, 1, d.m);
         HIP_TRY_JOB(hipGetLastError());
         HIP_TRY_JOB(nuts_init_state(d, x0, job->stream));
@@ -669,6 +670,15 @@ static fsmmc_status progress(fsmmc_job* job, std::vector<uint32_t>& t, std::vect
     return FSMMC_OK;
 }
 
+// Steps per launch of the NUTS block kernel (a few milliseconds): what a launch
+// adds, about 15 us, is below 1%, and no launch holds the GPU for long.
+constexpr int kBlockSteps = 1024;
+
+// Chains per block if the job's FSM runs on the block kernel, else 0.  With
+// tune.timing on the transition and the gradient stay launches of their own, so
+// that their times can be told apart.
+static int nuts_block(const fsmmc_job* job) { return job->timing ? 0 : nuts_block_chains(job->d, job->d.m); }
+
 // NUTS runtime: steps of {transition (and request list), gradient}, issued in
 // batches; after each batch the host reads how many chains are still alive
 // and how many asked for a gradient in the last step.
@@ -684,11 +694,16 @@ static fsmmc_status nuts_run(fsmmc_job* job, int mode, int64_t max_steps, uint32
     const int batch = 16;
     uint32_t* h = reinterpret_cast<uint32_t*>(job->h_ctr + 8);
     uint32_t alive = 1;
+    const int G = mode == 0 ? nuts_block(job) : 0;
     for (;;) {
-        for (int i = 0; i < batch; ++i) {
+        for (int i = 0; i < (G ? 0 : batch); ++i) {
             const uint32_t s = job->step;
             HIP_TRY(launch(job, mode == 0 ? KC_FSM : KC_SYNC, [&] { return nuts_transition(d, mode, s, job->stream); }));
             HIP_TRY(launch(job, KC_G, [&] { return nuts_gradient(d, mode, s, job->stream); }));
+            job->step++;
+        }
+        if (G) {
+            HIP_TRY(launch(job, KC_FSM, [&] { return nuts_block_steps(d, G, kBlockSteps, job->step, job->stream); }));
             job->step++;
         }
         HIP_TRY(hipMemcpyAsync(h, d.wctr, 9 * 4, hipMemcpyDeviceToHost, job->stream));
@@ -955,7 +970,14 @@ fsmmc_status fsmmc_step_fsm_async(fsmmc_job* job, int64_t max_steps, int32_t* do
     job->launches++;
     if (nuts_lr) {
         HIP_TRY(fill_i32((int32_t*)d.wctr + 6, 0, 3, s));
-        for (int64_t i = 0; i <= max_steps; ++i) {
+        const int G = nuts_block(job);
+        for (int64_t i = 0; G && i <= max_steps; i += kBlockSteps) {
+            const uint32_t st = job->step;
+            const int K = (int)std::min<int64_t>(kBlockSteps, max_steps + 1 - i);
+            HIP_TRY(launch(job, KC_FSM, [&] { return nuts_block_steps(d, G, K, st, s); }));
+            job->step++;
+        }
+        for (int64_t i = 0; !G && i <= max_steps; ++i) {
             const uint32_t st = job->step;
             HIP_TRY(launch(job, KC_FSM, [&] { return nuts_transition(d, 0, st, s); }));
             HIP_TRY(launch(job, KC_G, [&] { return nuts_gradient(d, 0, st, s); }));

@@ -112,6 +112,9 @@ int ess_supported_epl(int D, int dtype);
 int nuts_nvec(int max_depth);
 hipError_t nuts_init_state(const JobDev& j, const void* x0, hipStream_t s);
 hipError_t nuts_transition(const JobDev& j, int mode, uint32_t step, hipStream_t s);
+int nuts_block_chains(const JobDev& j, int64_t chains);  // chains: of the jobs that run at once
+hipError_t nuts_block_setup(const JobDev& j);
+hipError_t nuts_block_steps(const JobDev& j, int G, int K, uint32_t step, hipStream_t s);
 hipError_t nuts_gradient(const JobDev& j, int mode, uint32_t step, hipStream_t s);  // after nuts_transition(mode, step)
 size_t logreg_split_bytes(const JobDev& j);
 hipError_t logreg_setup(const JobDev& j, hipStream_t s);

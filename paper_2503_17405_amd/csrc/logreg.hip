@@ -38,7 +38,8 @@ __global__ __launch_bounds__(512) void logreg_grad_bf16_kernel(GradK a)
 }
 
 // X (Np x Dp FP32) -> three bf16 pieces in the two chunk layouts the kernel
-// above loads: per 32-row chunk, [p][row][d] then [p][d][row].
+// above loads: per 32-row chunk, [p] row units (8 values of d), then [p] column
+// units (8 rows), in GradB's memory order.
 template <int DP>
 __global__ void logreg_split_kernel(const float* X, int Np, uint16_t* Xb)
 {
@@ -47,12 +48,14 @@ __global__ void logreg_split_kernel(const float* X, int Np, uint16_t* Xb)
     const int row = (int)(i / DP), d = (int)(i % DP);
     uint32_t pc[3];
     split_bf16x3(X[i], pc[0], pc[1], pc[2]);
+    using S = GradB<DP / 32>;
     uint16_t* base = Xb + (size_t)(row / 32) * (192 * DP);
     const int r = row % 32;
+    const int ru = S::row_unit(r, d >> 3) * 8 + (d & 7), cu = S::col_unit(d, r >> 3) * 8 + (r & 7);
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
-        base[p * 32 * DP + r * DP + d] = (uint16_t)pc[p];
-        base[96 * DP + p * DP * 32 + d * 32 + r] = (uint16_t)pc[p];
+        base[p * 32 * DP + ru] = (uint16_t)pc[p];
+        base[96 * DP + p * DP * 32 + cu] = (uint16_t)pc[p];
     }
 }
 

@@ -49,6 +49,22 @@ struct GradB {
     }
     // unit permutation of a 64-byte column (d-major X, r)
     static __device__ __forceinline__ int colswz(int col) { return (col >> 1) & 3; }
+    // Order of a piece's 16-byte units in memory: unit u (8 values of d) of a row,
+    // unit u (8 rows) of a column d.  DT = 4: row by row, column by column.  DT = 2:
+    // in the order of the lanes that read them as matrix-core operands (row or
+    // column 16 i + (lane & 15), unit 4 k + lane / 16), so that the block kernel
+    // of nuts_block.h, which takes operands from memory, reads 1 KiB at a time
+    // (lanes 128 bytes apart took four times as long).
+    static __host__ __device__ __forceinline__ int row_unit(int row, int u)
+    {
+        if (DT != 2) return row * (DP / 8) + u;
+        return 128 * (row >> 4) + 64 * (u >> 2) + 16 * (u & 3) + (row & 15);
+    }
+    static __host__ __device__ __forceinline__ int col_unit(int d, int u)
+    {
+        if (DT != 2) return 4 * d + u;
+        return 64 * (d >> 4) + 16 * u + (d & 15);
+    }
 };
 
 __device__ __forceinline__ uint4 pack_bf16x8(const uint32_t (&v)[8])
@@ -132,13 +148,15 @@ __device__ __forceinline__ void logreg_grad_tile(const GradK& a, int ct, int sl,
     constexpr int NS = (NU + 255) / 256;       // per thread of a role (at most)
     static_assert(NS <= 6, "half-chunk share");
     const int rtid = tid & 255;
-    auto off_of = [&](int f) {
+    auto off_of = [&](int f) {  // unit f of the half in memory -> byte of the LDS image
+        const int p0 = f & ~(32 * DP / 8 - 1), g = f & (32 * DP / 8 - 1);  // piece, unit of the piece
         if (ewave) {
-            const int row = (f / (DP / 8)) & 31, u = f % (DP / 8);
-            return 16 * (f - u + (u ^ S::rowswz(row)));
+            const int row = DT == 2 ? 16 * (g >> 7) + (g & 15) : g / (DP / 8);
+            const int u = DT == 2 ? (g >> 4) & 7 : g % (DP / 8);
+            return 16 * (p0 + row * (DP / 8) + (u ^ S::rowswz(row)));
         }
-        const int d = (f >> 2) & (DP - 1), u = f & 3;
-        return 16 * (f - u + (u ^ S::colswz(d)));
+        const int d = DT == 2 ? 16 * (g >> 6) + (g & 15) : g >> 2, u = DT == 2 ? (g >> 4) & 3 : g & 3;
+        return 16 * (p0 + 4 * d + (u ^ S::colswz(d)));
     };
     int so[6];
 #pragma unroll

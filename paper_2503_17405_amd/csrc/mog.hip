@@ -179,7 +179,8 @@ __global__ __launch_bounds__(512) void nuts_mog_kernel(NutsK a, MogK mk, unsigne
         const uint32_t t = uni(a.t[c]);
         if (t >= a.tstop) continue;
         NutsScal S = nuts_load(a, c, t);
-        NutsBox<EPL, BOX_HELD> box(a.V + (size_t)c * a.nvec * a.Dp, a.Dp, lane);
+        float* Vc = a.V + (size_t)c * a.nvec * a.Dp;
+        NutsBox<EPL, BOX_HELD> box(Vc, a.Dp, lane, Vc + (size_t)V_FIXED * a.Dp);
         int bits;
         do {
             bits = nuts_chain_body<EPL, MogGrad, false, BOX_HELD>(a, G, c, lane, S, box);

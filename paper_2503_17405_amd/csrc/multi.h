@@ -48,11 +48,11 @@ struct fsmmc_batch {
     size_t cap_items = 0;
     fsmmc::BTile* d_tiles = nullptr;  // ellipse GEMM tiles
     size_t cap_tiles = 0;
-    fsmmc::BItem* d_nitems = nullptr;  // NUTS chains (EPL 1, then EPL 2)
+    fsmmc::BItem* d_nitems = nullptr;  // NUTS chains (EPL 1, then EPL 2, then the block kernel's blocks)
     size_t cap_nitems = 0;
     fsmmc::BGrad* d_grads = nullptr;  // NUTS gradient tiles (Dp 64, then Dp 128)
     size_t cap_grads = 0;
-    int32_t* d_njobs = nullptr;  // NUTS jobs (compaction blocks)
+    int32_t* d_njobs = nullptr;  // NUTS jobs that run a launch per step
     size_t cap_njobs = 0;
     unsigned char* d_stat = nullptr;  // header, then (live, draws) per job
     unsigned char* h_stat = nullptr;  // pinned mirror
@@ -60,6 +60,7 @@ struct fsmmc_batch {
     int n_items = 0, fsm_blocks = 0;
     int tile_off[fsmmc::kTileSlots] = {0}, tile_cnt[fsmmc::kTileSlots] = {0};
     int nstep_cnt[2] = {0, 0}, grad_cnt[2] = {0, 0}, n_nuts = 0;
+    int nblock_cnt = 0, nblock_lds = 0;  // NUTS block kernel: blocks, LDS bytes of the largest
     hipGraphExec_t exec = nullptr;
     bool dirty = true;
     int pending_k = 0;  // replays launched and not yet collected

@@ -24,7 +24,8 @@
 // Readings: multinomial leaf sampling inside a subtree, biased progressive
 // merge of subtrees, generalized U-turn criterion on every aligned sub-span,
 // divergence when H - H0 > 1000, identity mass.
-#include "nuts_device.h"
+#include "nuts_block.h"
+#include <algorithm>
 
 namespace fsmmc {
 
@@ -138,6 +139,73 @@ static void fsm_step(const NutsK& a, hipStream_t s)
         fsm_step_launch<EPL, 8, true>(a, s);
     else
         fsm_step_launch<EPL, 8, false>(a, s);
+}
+
+template <int NK32, int NT, int R>
+__global__ __launch_bounds__(64 * kNutsBlockWaves) void nuts_block_kernel(NutsK a, GradK g, int G, int K)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.rcnt[(a.step + 1) % 3] = 0u;
+    nuts_block_run<NK32, NT, R>(a, g, (int)blockIdx.x * G, G, K, lds, a.rcnt + a.step % 3);
+}
+
+// Chains per block of the block kernel, or 0: the job runs a launch per step.
+// `chains` compete for the 256 compute units: as few per block as give every unit
+// one, at most 8, then several rounds of blocks.  A step's cost in cycles is the
+// transition (6000) and per 32-row chunk the 6 k-step and 3 d-tile KiB that each
+// unit reads at 64 bytes a cycle, against 20 us or so for a step of two launches.
+// Below the line at 40000: 16 chains, N = 1000, D = 10 (one round, 10600): 6.1 ->
+// 1.8 ms for 40 draws; 4096 chains, N = 2000, D = 20 (two rounds, 36200): 3.9 ->
+// 2.8; 4096, N = 1000, D = 50 (36600): 6.3 -> 5.5.  Above: N = 8000, D = 20 (54000):
+// 16 chains 5.9 -> 4.8 but 256 chains 2.75 -> 3.2; N = 4000, D = 50 (54000): 8.4 ->
+// 9.9; 16384 chains, N = 1000, D = 10 (eight rounds, 85000): 4.3 -> 7.5.
+int nuts_block_chains(const JobDev& j, int64_t chains)
+{
+    if (j.EPL != 1) return 0;
+    const int nt = nuts_block_class(j.D), nk32 = (nt + 1) / 2, chunks = (j.N + 31) / 32;
+    const int64_t G = std::min<int64_t>(kNutsBlockWaves, (chains + 255) / 256);
+    const int64_t rounds = (chains + 256 * G - 1) / (256 * G);
+    if (rounds * (6000 + (int64_t)chunks * 48 * (2 * nk32 + nt)) > 40000) return 0;
+    return nuts_block_lds((int)G, j.nslices, nt, j.max_depth).bytes <= kNutsBlockLds ? (int)G : 0;
+}
+
+constexpr int kNutsHeld = 4;
+// Whether the waves' shares of X fit their registers.
+static bool nuts_block_held(const JobDev& j, int G)
+{
+    int lgp = 0;
+    while ((1 << lgp) < G) ++lgp;
+    const int per = (j.nslices + kNutsBlockWaves - 1) / kNutsBlockWaves;
+    return j.slice_rows == 32 && per <= kNutsHeld && per <= (16 >> lgp);
+}
+
+template <int NK32, int NT, int R>
+static hipError_t block_launch(const JobDev& j, const NutsK& a, int G, int K, hipStream_t s, bool setup)
+{
+    const void* f = (const void*)nuts_block_kernel<NK32, NT, R>;
+    if (setup) return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kNutsBlockLds);
+    hipLaunchKernelGGL((nuts_block_kernel<NK32, NT, R>), dim3((j.m + G - 1) / G), dim3(64 * kNutsBlockWaves),
+                       nuts_block_lds(G, j.nslices, NT, j.max_depth).bytes, s, a, grad_view(j, 0), G, K);
+    return hipGetLastError();
+}
+
+static hipError_t block_dispatch(const JobDev& j, const NutsK& a, int G, int K, hipStream_t s, bool setup)
+{
+    switch (nuts_block_class(j.D)) {
+    case 1:
+        if (nuts_block_held(j, G)) return block_launch<1, 1, kNutsHeld>(j, a, G, K, s, setup);
+        return block_launch<1, 1, 0>(j, a, G, K, s, setup);
+    case 2: return block_launch<1, 2, 0>(j, a, G, K, s, setup);
+    case 3: return block_launch<2, 3, 0>(j, a, G, K, s, setup);
+    default: return block_launch<2, 4, 0>(j, a, G, K, s, setup);
+    }
+}
+
+hipError_t nuts_block_setup(const JobDev& j) { return block_dispatch(j, NutsK{}, nuts_block_chains(j, j.m), 0, nullptr, true); }
+
+hipError_t nuts_block_steps(const JobDev& j, int G, int K, uint32_t step, hipStream_t s)
+{
+    return block_dispatch(j, nuts_view(j, 0, step), G, K, s, false);
 }
 
 hipError_t nuts_transition(const JobDev& j, int mode, uint32_t step, hipStream_t s)

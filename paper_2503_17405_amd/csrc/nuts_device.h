@@ -23,7 +23,7 @@ __device__ __forceinline__ float logaddexp_f(float a, float b)
 }
 
 struct NutsK {
-    int m, n, D, Dp, J, nvec, ckp0, ckr0, mode;
+    int m, n, D, Dp, J, nvec, mode;
     uint32_t step, tstop;
     uint64_t seed;
     float eps;
@@ -180,9 +180,11 @@ template <int EPL, int BOX>
 struct NutsBox {
     float* Vc;
     int Dp, lane;
+    float* ck;  // U-turn checkpoints: momentum of level lev at row lev - 1, rho at J + lev - 1
     WaveVec<EPL> r[BOX == BOX_MEMORY ? 1 : V_FIXED];
 
-    __device__ __forceinline__ NutsBox(float* v, int dp, int l) : Vc(v), Dp(dp), lane(l)
+    // v: the chain's vectors, ckpt: its checkpoints (in memory they lie behind the vectors)
+    __device__ __forceinline__ NutsBox(float* v, int dp, int l, float* ckpt) : Vc(v), Dp(dp), lane(l), ck(ckpt)
     {
         if constexpr (BOX != BOX_MEMORY) {
 #pragma unroll
@@ -250,7 +252,8 @@ template <int EPL, class Grad, bool PRE = false, int BOX = BOX_MEMORY>
 __device__ __forceinline__ int nuts_chain_body(const NutsK& a, const Grad& grad, int c, int lane, NutsScal& S,
                                                NutsBox<EPL, BOX>& box, const NutsPre<EPL>* pre = nullptr)
 {
-    auto vec = [&](int i) { return box.Vc + (size_t)i * a.Dp; };  // U-turn checkpoints
+    auto ckp_at = [&](int lev) { return box.ck + (lev - 1) * a.Dp; };
+    auto ckr_at = [&](int lev) { return box.ck + (a.J + lev - 1) * a.Dp; };
     uint32_t t = S.t;
     int k = S.k, j = S.j, v = S.v, nn = S.nn, fl = S.fl, nleap = S.nleap;
     int64_t budget = S.budget;
@@ -308,15 +311,15 @@ __device__ __forceinline__ int nuts_chain_body(const NutsK& a, const Grad& grad,
                     WaveVec<EPL> ck;
 #pragma unroll
                     for (int e = 0; e < EPL; ++e) ck.r[e] = rs.r[e] - p.r[e];
-                    p.store(vec(a.ckp0 + lev), lane);
-                    ck.store(vec(a.ckr0 + lev), lane);
+                    p.store(ckp_at(lev), lane);
+                    ck.store(ckr_at(lev), lane);
                 }
             }
             for (int lev = 1; lev <= j; ++lev) {
                 if (((nn + 1) & ((1 << lev) - 1)) == 0) {
                     WaveVec<EPL> ckp, span;
-                    ckp.load(vec(a.ckp0 + lev), lane);
-                    span.load(vec(a.ckr0 + lev), lane);
+                    ckp.load(ckp_at(lev), lane);
+                    span.load(ckr_at(lev), lane);
 #pragma unroll
                     for (int e = 0; e < EPL; ++e) span.r[e] = rs.r[e] - span.r[e];
                     if (wdot(ckp, span) <= 0.0f || wdot(p, span) <= 0.0f) fl |= NF_INVALID | NF_TURNED;
@@ -494,7 +497,8 @@ __device__ __forceinline__ int nuts_chain_step(const NutsK& a, const Grad& grad,
         if (lane == 0) a.req[c] = 0;
         return 0;
     }
-    NutsBox<EPL, BOX_MEMORY> box(a.V + (size_t)c * a.nvec * a.Dp, a.Dp, lane);
+    float* Vc = a.V + (size_t)c * a.nvec * a.Dp;
+    NutsBox<EPL, BOX_MEMORY> box(Vc, a.Dp, lane, Vc + (size_t)V_FIXED * a.Dp);
     const int bits = nuts_chain_body<EPL, Grad>(a, grad, c, lane, S, box);
     nuts_store(a, c, S, (bits & NC_REQ) ? 1 : 0, lane);
     return bits;
@@ -512,7 +516,7 @@ __device__ __forceinline__ int nuts_chain_step(const NutsK& a, int c, int lane)
 {
     c = uni(c);
     float* Vc = a.V + (size_t)c * a.nvec * a.Dp;
-    NutsBox<EPL, AHEAD ? BOX_AHEAD : BOX_MEMORY> box(Vc, a.Dp, lane);
+    NutsBox<EPL, AHEAD ? BOX_AHEAD : BOX_MEMORY> box(Vc, a.Dp, lane, Vc + (size_t)V_FIXED * a.Dp);
     NutsPre<EPL> P;
     if constexpr (!AHEAD) {
         P.ph.load(Vc + (size_t)V_PH * a.Dp, lane);
@@ -613,8 +617,6 @@ inline NutsK nuts_view(const JobDev& j, int mode, uint32_t step)
     a.Dp = j.Dp;
     a.J = j.max_depth;
     a.nvec = j.nvec;
-    a.ckp0 = V_FIXED - 1;  // level lev in [1, J] lives at ckp0 + lev
-    a.ckr0 = V_FIXED - 1 + j.max_depth;
     a.mode = mode;
     a.step = step;
     a.tstop = j.tstop;

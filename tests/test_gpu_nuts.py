@@ -29,11 +29,11 @@ def ctx(F):
     c.close()
 
 
-def gpu_nuts(F, ctx, d, m, n, seed, eps, J, x0=None, runtime="fsm", max_steps=0, out=None):
+def gpu_nuts(F, ctx, d, m, n, seed, eps, J, x0=None, runtime="fsm", max_steps=0, out=None, timing=False):
     X = torch.tensor(d["X"], dtype=torch.float32, device="cuda")
     y = torch.tensor(d["y"], dtype=torch.float32, device="cuda")
     x0t = None if x0 is None else torch.tensor(np.asarray(x0), dtype=torch.float32, device="cuda")
-    job = F.Job(ctx, F.logreg_target(X, y), F.nuts_sampler(eps, J), m, n, seed, x0=x0t, out=out)
+    job = F.Job(ctx, F.logreg_target(X, y), F.nuts_sampler(eps, J), m, n, seed, x0=x0t, out=out, timing=timing)
     try:
         if runtime == "fsm":
             for _ in range(100000):
@@ -207,9 +207,52 @@ def test_nuts_request_lists_at_block_edges(F, ctx, m, D):
     lists, against the synchronized runtime's list in chain order: same bits,
     whole and in pieces of 5 gradients, with partly filled last blocks."""
     d = inputs.logreg(n_data=64, dim=D, seed=3)
-    S, C, st = gpu_nuts(F, ctx, d, m, 6, 11, 0.2, 4)
-    S1, C1, st1 = gpu_nuts(F, ctx, d, m, 6, 11, 0.2, 4, max_steps=5)
+    # timing=True: a launch per step at every size
+    S, C, st = gpu_nuts(F, ctx, d, m, 6, 11, 0.2, 4, timing=True)
+    S1, C1, st1 = gpu_nuts(F, ctx, d, m, 6, 11, 0.2, 4, max_steps=5, timing=True)
     S2, C2, _ = gpu_nuts(F, ctx, d, m, 6, 11, 0.2, 4, runtime="compact")
     assert np.array_equal(C, C2) and np.array_equal(S, S2)
     assert np.array_equal(C, C1) and np.array_equal(S, S1)
     assert st["steps"] == st1["steps"] == int(C.sum())
+
+
+# every dimension class of the block kernel and its edges; rows that fill one chunk
+# or part of it, slices of one and of many chunks, a short last slice; one chain per
+# block, several (columns shared by chains and slices), a partly filled last block
+@pytest.mark.parametrize("D,N,m", [(1, 1, 1), (16, 32, 3), (17, 33, 300), (32, 1000, 16), (33, 257, 520), (48, 500, 9),
+                                   (49, 300, 1030), (64, 700, 5), (10, 1000, 2049), (20, 2000, 1100), (5, 4500, 70)])
+def test_nuts_block_kernel_equals_launch_per_step(F, ctx, D, N, m):
+    d = inputs.logreg(n_data=N, dim=D, seed=5)
+    n, seed, eps, J = 5, 21, 0.1, 5
+    S, C, st = gpu_nuts(F, ctx, d, m, n, seed, eps, J)
+    S1, C1, st1 = gpu_nuts(F, ctx, d, m, n, seed, eps, J, timing=True)
+    S2, C2, st2 = gpu_nuts(F, ctx, d, m, n, seed, eps, J, max_steps=7)
+    assert np.isfinite(S).all()
+    for s, c, r in ((S1, C1, st1), (S2, C2, st2)):
+        assert np.array_equal(S, s) and np.array_equal(C, c)
+        assert st["steps"] == r["steps"] == int(C.sum())
+
+
+@pytest.mark.parametrize("D,N,m", [(10, 1000, 16), (20, 300, 300), (64, 90, 9)])
+def test_nuts_block_kernel_hands_over(F, ctx, D, N, m):
+    """A batch's block kernel leaves chains with a gradient pending after each
+    round; the launch per step (timing=True) and the single-job block kernel
+    take them over, and the other way round."""
+    d = inputs.logreg(n_data=N, dim=D, seed=6)
+    X = torch.tensor(d["X"], dtype=torch.float32, device="cuda")
+    y = torch.tensor(d["y"], dtype=torch.float32, device="cuda")
+    n, seed, eps, J = 8, 22, 0.1, 5
+    S, C, st = gpu_nuts(F, ctx, d, m, n, seed, eps, J, timing=True)
+    for timing in (True, False):
+        job = F.Job(ctx, F.logreg_target(X, y), F.nuts_sampler(eps, J), m, n, seed, timing=timing)
+        try:
+            for piece in (3, 11):
+                b = F.Batch(ctx, [job], nuts_steps=5)
+                b.run(2)
+                b.free()
+                job.step_fsm(piece)
+            assert job.step_fsm(0)
+            assert np.array_equal(job.samples(), S) and np.array_equal(job.counts(), C)
+            assert job.stats()["steps"] == st["steps"]
+        finally:
+            job.free()
