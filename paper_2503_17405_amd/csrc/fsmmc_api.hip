@@ -132,7 +132,10 @@ static fsmmc_status scratch_setup(int device, void** out)
     return FSMMC_OK;
 }
 
-static fsmmc_status job_alloc(fsmmc_job* j, size_t bytes, void** p)
+// Device memory of a job.  zero: cleared.  Small arrays are cut from zeroed slabs:
+// a job has about twenty, and an allocation, a clear and a free of each were a
+// third of a millisecond.  The budget counts what was asked for.
+static fsmmc_status job_alloc(fsmmc_job* j, size_t bytes, void** p, bool zero = true)
 {
     *p = nullptr;
     if (bytes == 0) bytes = 256;
@@ -146,34 +149,128 @@ static fsmmc_status job_alloc(fsmmc_job* j, size_t bytes, void** p)
     } else {
         c->used.fetch_add(bytes);
     }
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) {
-        c->used.fetch_sub(bytes);
-        *p = nullptr;
-        return fail(FSMMC_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+    // sixteen arrays of 8 bytes per chain, 256 KiB to 8 MiB
+    const size_t slab = std::min<size_t>(8u << 20, std::max<size_t>(256u << 10, (size_t)j->d.m * 128));
+    const size_t cut = (bytes + 255) & ~(size_t)255;
+    hipError_t e = hipSuccess;
+    if (cut <= slab / 4) {
+        if (j->slab_left < cut) {
+            void* q = nullptr;
+            if (hipMalloc(&q, slab) == hipSuccess) {
+                j->allocs.push_back(q);
+                j->slab = (unsigned char*)q;
+                j->slab_left = slab;
+                e = hipMemsetAsync(q, 0, slab, j->stream);
+            } else {
+                (void)hipGetLastError();  // the array alone may still fit
+            }
+        }
+        if (j->slab_left >= cut) {
+            *p = j->slab;
+            j->slab += cut;
+            j->slab_left -= cut;
+        }
     }
-    j->allocs.push_back(*p);
+    if (!*p) {
+        e = hipMalloc(p, bytes);
+        if (e != hipSuccess) {
+            c->used.fetch_sub(bytes);
+            *p = nullptr;
+            return fail(FSMMC_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+        }
+        j->allocs.push_back(*p);
+        if (zero) e = hipMemsetAsync(*p, 0, bytes, j->stream);
+    }
     j->bytes += bytes;
-    e = hipMemsetAsync(*p, 0, bytes, j->stream);
     if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
     return FSMMC_OK;
+}
+
+static fsmmc_status job_alloc_to(fsmmc_job* j, void** p, size_t bytes, bool zero = true)
+{
+    return job_alloc(j, bytes, p, zero);
+}
+
+// The job's pinned words: a slot of the context's page, or an allocation.
+static hipError_t pinned_take(fsmmc_job* j)
+{
+    fsmmc_ctx* c = j->ctx;
+    {
+        std::lock_guard<std::mutex> lk(c->mu);
+        if (!c->pinned) {
+            if (hipHostMalloc((void**)&c->pinned, fsmmc_ctx::kPinnedSlots * 128, hipHostMallocDefault) == hipSuccess)
+                c->pinned_free = ~0u;
+            else
+                (void)hipGetLastError();
+        }
+        if (c->pinned_free) {
+            const int i = __builtin_ctz(c->pinned_free);
+            c->pinned_free &= ~(1u << i);
+            j->h_ctr = c->pinned + 16 * i;
+            return hipSuccess;
+        }
+    }
+    return hipHostMalloc((void**)&j->h_ctr, 16 * sizeof(unsigned long long), hipHostMallocDefault);
+}
+
+static void pinned_give(fsmmc_job* j)
+{
+    fsmmc_ctx* c = j->ctx;
+    if (!j->h_ctr) return;
+    const ptrdiff_t i = c->pinned ? (j->h_ctr - c->pinned) / 16 : -1;
+    if (c->pinned && j->h_ctr >= c->pinned && i < fsmmc_ctx::kPinnedSlots) {
+        std::lock_guard<std::mutex> lk(c->mu);
+        c->pinned_free |= 1u << i;
+    } else {
+        (void)hipHostFree(j->h_ctr);
+    }
+}
+
+// The side stream and events of an ESS job that runs more than one window.
+static fsmmc_status side_open(fsmmc_job* j)
+{
+    if (!j->ev_snap) HIP_TRY(hipEventCreateWithFlags(&j->ev_snap, hipEventDisableTiming));
+    if (!j->ev_gemm) HIP_TRY(hipEventCreateWithFlags(&j->ev_gemm, hipEventDisableTiming));
+    if (j->side) return FSMMC_OK;
+    {
+        std::lock_guard<std::mutex> lk(j->ctx->mu);
+        if (!j->ctx->idle_streams.empty()) {
+            j->side = j->ctx->idle_streams.back();
+            j->ctx->idle_streams.pop_back();
+            return FSMMC_OK;
+        }
+    }
+    HIP_TRY(hipStreamCreateWithFlags(&j->side, hipStreamNonBlocking));
+    return FSMMC_OK;
+}
+
+static void side_close(fsmmc_job* j)
+{
+    if (!j->side) return;
+    const bool idle = hipStreamSynchronize(j->side) == hipSuccess;
+    if (idle) {
+        std::lock_guard<std::mutex> lk(j->ctx->mu);
+        if (j->ctx->idle_streams.size() < fsmmc_ctx::kIdleStreams) {
+            j->ctx->idle_streams.push_back(j->side);
+            j->side = nullptr;
+        }
+    }
+    if (j->side) (void)hipStreamDestroy(j->side);
+    j->side = nullptr;
 }
 
 static void job_release(fsmmc_job* j)
 {
     if (!j) return;
-    if (j->stream) (void)hipStreamSynchronize(j->stream);
+    (void)hipStreamSynchronize(j->stream);
+    side_close(j);
     for (void* p : j->allocs) (void)hipFree(p);
-    if (j->h_ctr) (void)hipHostFree(j->h_ctr);
+    pinned_give(j);
     for (const TimedLaunch& t : j->pending) {
         (void)hipEventDestroy(t.a);
         (void)hipEventDestroy(t.b);
     }
     for (hipEvent_t e : j->pool) (void)hipEventDestroy(e);
-    if (j->side) {
-        (void)hipStreamSynchronize(j->side);
-        (void)hipStreamDestroy(j->side);
-    }
     if (j->ev_snap) (void)hipEventDestroy(j->ev_snap);
     if (j->ev_gemm) (void)hipEventDestroy(j->ev_gemm);
     if (j->ctx) {
@@ -183,10 +280,10 @@ static void job_release(fsmmc_job* j)
     delete j;
 }
 
-#define ALLOC(ptr, bytes)                                               \
+#define ALLOC(ptr, ...)                                                 \
     do {                                                                \
         void* p__ = nullptr;                                            \
-        fsmmc_status s__ = job_alloc(job, (bytes), &p__);               \
+        fsmmc_status s__ = job_alloc_to(job, &p__, __VA_ARGS__);        \
         if (s__ != FSMMC_OK) {                                          \
             job_release(job);                                           \
             return s__;                                                 \
@@ -231,6 +328,8 @@ fsmmc_status fsmmc_ctx_destroy(fsmmc_ctx* ctx)
 {
     if (!ctx) return fail(FSMMC_EINVAL, "ctx is NULL");
     if (ctx->jobs.load() != 0) return fail(FSMMC_EBUSY, "context still has jobs");
+    for (hipStream_t st : ctx->idle_streams) (void)hipStreamDestroy(st);
+    if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     delete ctx;
     return FSMMC_OK;
 }
@@ -325,54 +424,7 @@ fsmmc_status fsmmc::validate_specs(const fsmmc_target_spec* t, const fsmmc_sampl
     return fail(FSMMC_EINVAL, "unknown sampler kind");
 }
 
-// Copy a dim x dim matrix (device, row-major) into a zero-padded Dp x Dp
-// lower-triangular device buffer (entries above the diagonal dropped).
 extern "C" {
-
-// The lower triangle of L, zero padded to Dp x Dp.  With `planes`, also its
-// exact three-piece bf16 split (hi, mid, lo; the same truncations as the
-// device's split of z) for the bf16 ellipse GEMM, packed per (row tile ti,
-// chunk c <= ti, k-block kb, piece p) as 32 x 16 blocks [row][k].
-static fsmmc_status stage_lower(fsmmc_job* job, const void* src, int D, int Dp, size_t es, void* dst,
-                                void* planes)
-{
-    std::vector<unsigned char> h((size_t)D * D * es), p((size_t)Dp * Dp * es, 0);
-    HIP_TRY(hipMemcpy(h.data(), src, h.size(), hipMemcpyDeviceToHost));
-    for (int r = 0; r < D; ++r) std::memcpy(&p[(size_t)r * Dp * es], &h[(size_t)r * D * es], (size_t)(r + 1) * es);
-    HIP_TRY(hipMemcpyAsync(dst, p.data(), p.size(), hipMemcpyHostToDevice, job->stream));
-    std::vector<uint16_t> pl;
-    if (planes) {
-        pl.assign(ess_lower_pieces_halfwords(Dp), 0);
-        const int nt = Dp / 32;
-        size_t blk = 0;  // ((ti (ti + 1) / 2 + c) 2 + kb) 3 + piece
-        for (int ti = 0; ti < nt; ++ti)
-            for (int c = 0; c <= ti; ++c)
-                for (int kb = 0; kb < 2; ++kb, blk += 3)
-                    for (int r = 0; r < 32; ++r)
-                        for (int kk = 0; kk < 16; ++kk) {
-                            float x;
-                            std::memcpy(&x, &p[((size_t)(32 * ti + r) * Dp + 32 * c + 16 * kb + kk) * 4], 4);
-                            uint32_t u, v, w;
-                            std::memcpy(&u, &x, 4);
-                            const uint32_t uh = u & 0xFFFF0000u;
-                            float fh, fm;
-                            std::memcpy(&fh, &uh, 4);
-                            const float r1 = x - fh;
-                            std::memcpy(&v, &r1, 4);
-                            const uint32_t um = v & 0xFFFF0000u;
-                            std::memcpy(&fm, &um, 4);
-                            const float r2 = r1 - fm;
-                            std::memcpy(&w, &r2, 4);
-                            const size_t at = 16 * r + kk;
-                            pl[blk * 512 + at] = (uint16_t)(uh >> 16);
-                            pl[(blk + 1) * 512 + at] = (uint16_t)(um >> 16);
-                            pl[(blk + 2) * 512 + at] = (uint16_t)(w >> 16);
-                        }
-        HIP_TRY(hipMemcpyAsync(planes, pl.data(), pl.size() * 2, hipMemcpyHostToDevice, job->stream));
-    }
-    HIP_TRY(hipStreamSynchronize(job->stream));
-    return FSMMC_OK;
-}
 
 fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
                                const fsmmc_sampler_spec* sampler, int32_t n_chains, int32_t n_draws,
@@ -407,7 +459,7 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
     const size_t es = d.dtype == FSMMC_F32 ? 4 : 8;
     const size_t m = (size_t)d.m;
 
-    HIP_TRY_JOB(hipHostMalloc((void**)&job->h_ctr, 16 * sizeof(unsigned long long), hipHostMallocDefault));
+    HIP_TRY_JOB(pinned_take(job));
     ALLOC(d.ctr, 8 * sizeof(unsigned long long));
     ALLOC(d.k, m * 4);
     ALLOC(d.t, m * 4);
@@ -468,16 +520,15 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         d.W = std::max(1, std::min(W, d.n));
         while ((int64_t)d.W * d.m > (int64_t)1 << 30 && d.W > 1) d.W /= 2;
         d.Wcap = d.W;
-        ALLOC(d.nu, 2 * m * (size_t)d.W * Dp * es);
+        ALLOC(d.nu, 2 * m * (size_t)d.W * Dp * es, false);  // a window is filled before it is read
         ALLOC(d.tsnap, m * 4);
-        HIP_TRY_JOB(hipStreamCreateWithFlags(&job->side, hipStreamNonBlocking));
-        HIP_TRY_JOB(hipEventCreateWithFlags(&job->ev_snap, hipEventDisableTiming));
-        HIP_TRY_JOB(hipEventCreateWithFlags(&job->ev_gemm, hipEventDisableTiming));
-        fsmmc_status s2 = stage_lower(job, target->chol_L, d.D, d.Dp, es, d.L, d.Lp);
-        if (s2 != FSMMC_OK) {
-            job_release(job);
-            return s2;
-        }
+        // chol_L is read as a synchronous copy would read it: after the work of the
+        // null stream, and done when this returns
+        HIP_TRY_JOB(hipStreamSynchronize(nullptr));
+        HIP_TRY_JOB(hipMemcpy2DAsync(d.L, Dp * es, target->chol_L, (size_t)d.D * es, (size_t)d.D * es, (size_t)d.D,
+                                     hipMemcpyDefault, job->stream));
+        HIP_TRY_JOB(ess_stage_lower(d, job->stream));
+        HIP_TRY_JOB(hipStreamSynchronize(job->stream));
         HIP_TRY_JOB(hipMemcpyAsync(d.y, target->y, (size_t)d.D * es, hipMemcpyDeviceToDevice, job->stream));
         // k = S_1 (INIT), t = 0
         hipLaunchKernelGGL(fill_i32_kernel, dim3((d.m + 255) / 256), dim3(256), 0, job->stream, d.k, 1, d.m);
@@ -823,6 +874,10 @@ static fsmmc_status ess_windows(fsmmc_job* job, int mode, uint32_t t0, uint32_t 
     JobDev& d = job->d;
     hipStream_t s = job->stream;
     d.nu_cur = 0;
+    if (K > 1) {
+        fsmmc_status st = side_open(job);
+        if (st != FSMMC_OK) return st;
+    }
     HIP_TRY(launch(job, KC_G, [&] { return ess_fill_window(d, s); }));
     for (int k = 0; k < K; ++k) {
         const bool next = k + 1 < K;

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -17,6 +18,15 @@ struct fsmmc_ctx {
     size_t budget = 0;
     std::atomic<size_t> used{0};
     std::atomic<int> jobs{0};
+    // Handed from freed jobs to new ones (creating them costs more than a small
+    // job): side streams with nothing queued, and the slots of one pinned page.
+    // Released with the context, which outlives its jobs.
+    static constexpr size_t kIdleStreams = 8;
+    static constexpr int kPinnedSlots = 32;  // of 16 64-bit words
+    std::mutex mu;
+    std::vector<hipStream_t> idle_streams;
+    unsigned long long* pinned = nullptr;
+    uint32_t pinned_free = 0;  // bit i: slot i is free
 };
 
 namespace fsmmc {
@@ -53,6 +63,8 @@ struct fsmmc_job {
     fsmmc::JobDev d;
     std::vector<void*> allocs;
     size_t bytes = 0;
+    unsigned char* slab = nullptr;  // zeroed memory not handed out yet (job_alloc)
+    size_t slab_left = 0;
     unsigned long long* h_ctr = nullptr;  // pinned: [0..7] mirror of d.ctr, [8..15] scratch reads
     int launches = 0;
     uint32_t step = 0;  // NUTS runtime step counter (keys the per-step counters)

@@ -107,6 +107,9 @@ hipError_t ess_fsm_round(const JobDev& j, hipStream_t s);
 hipError_t ess_sync_draw(const JobDev& j, uint32_t draw, uint32_t slot, hipStream_t s);
 hipError_t ess_pad_draw(const JobDev& j, uint32_t draw, uint32_t slot, hipStream_t s);
 int ess_supported_epl(int D, int dtype);
+// d.L (dim x dim in Dp x Dp, zero padded): drop the part above the diagonal, and
+// fill Lp, if the job has it, with the bf16 pieces.
+hipError_t ess_stage_lower(const JobDev& d, hipStream_t s);
 
 // NUTS launchers (nuts.hip); mode 0 = FSM, 1 = synchronized vmap, 2 = synchronized compact
 int nuts_nvec(int max_depth);

@@ -262,3 +262,46 @@ def test_ess_argument_errors(F, ctx):
         assert small.bytes_in_use() == 0
     finally:
         small.close()
+
+
+def test_ess_many_jobs_share_a_context(F):
+    """More live jobs than the context keeps pinned slots and side streams for,
+    stepped and freed from several threads, in two waves: the draws of a job
+    on its own.  chol_L with entries above the diagonal, which are not read."""
+    import threading
+    c = F.Context(0)
+    w = inputs.gp_logistic(dim=70, seed=3)
+    L, y = _dev(w["L"], torch.float32), _dev(w["y"], torch.float32)
+    L = L + torch.triu(torch.full_like(L, 7.0), 1)
+    torch.cuda.synchronize()
+    m, n = 9, 12
+    try:
+        def draws(seed, out):
+            job = F.Job(c, F.gp_target(L, y), F.ess_sampler(F.F32), m, n, seed, window=4, stream=None)
+            live.append(job)
+            job.step_fsm(0)
+            out[seed] = job.samples()
+
+        live, alone = [], {}
+        for seed in range(40):
+            draws(seed, alone)
+            live.pop().free()
+        S, _, _ = gpu_ess(F, c, w, m, n, 5)
+        assert np.array_equal(alone[5], S)
+        for _ in range(2):
+            live, got = [], {}
+            for seed in range(34):  # past the pinned page's 32 slots
+                draws(seed, got)
+            ts = [threading.Thread(target=draws, args=(seed, got)) for seed in range(34, 40)]
+            for t in ts:
+                t.start()
+            for t in ts:
+                t.join()
+            assert sorted(got) == list(range(40))
+            for seed in range(40):
+                assert np.array_equal(got[seed], alone[seed]), seed
+            for job in live:
+                job.free()
+        assert c.bytes_in_use() == 0
+    finally:
+        c.close()
