@@ -256,3 +256,57 @@ def test_nuts_block_kernel_hands_over(F, ctx, D, N, m):
             assert job.stats()["steps"] == st["steps"]
         finally:
             job.free()
+
+
+# every dimension class of the gradient kernel (8 dimensions each) and partly filled
+# ones; less than a chunk of rows, a few chunks, several slices; chain tiles of
+# 128 partly filled.  FP64 reference; the bounds are FP32's: a sum of N terms of
+# size |X_id| <= 5, |eta| < 40, accumulated in chunks of 32 rows
+@pytest.mark.parametrize("D", [1, 5, 8, 13, 16, 17, 24, 31, 40, 41, 48, 56, 64, 65, 72, 79, 80, 88, 96, 97, 104, 112, 120, 128])
+def test_potential_every_dimension_class(F, ctx, D):
+    for N, m in ((20, 140), (70, 33), (3000, 129)):
+        gen = torch.Generator().manual_seed(1000 * D + N)
+        X = torch.randn(N, D, generator=gen).clamp(-5, 5)
+        y = (torch.rand(N, generator=gen) > 0.5).float()
+        th = 0.3 * torch.randn(m, D, generator=gen)
+        job = F.Job(ctx, F.logreg_target(X.cuda(), y.cuda()), F.nuts_sampler(0.1, 5), m, 1, 1)
+        try:
+            U, g = job.potential(th.cuda())
+            U1, g1 = torch.empty_like(U), torch.empty_like(g)
+            job.potential_noalloc(th.cuda(), g1, U1)
+            job.sync()
+            Uh, gh = job.potential(th)  # host memory: copied, the same bits
+        finally:
+            job.free()
+        assert torch.equal(U, U1) and torch.equal(g, g1)
+        assert torch.equal(U.cpu(), Uh) and torch.equal(g.cpu(), gh)
+        Xd, yd, td = X.double(), y.double()[:, None], th.double()
+        eta = Xd @ td.T
+        Ur = 0.5 * (td ** 2).sum(1) - (yd * eta - torch.nn.functional.softplus(eta)).sum(0)
+        gr = td - (yd - torch.sigmoid(eta)).T @ Xd
+        scale = (Xd.abs().sum(0) + 1.0)[None, :]
+        assert ((g.cpu().double() - gr).abs() / scale).max() < 1e-5
+        assert ((U.cpu().double() - Ur).abs() / (1.0 + eta.abs().sum(0) + N)).max() < 1e-6
+
+
+@pytest.mark.parametrize("D", [8, 24, 40, 56, 72, 88, 104, 120])
+def test_launch_per_step_every_dimension_class(F, ctx, D):
+    """The single-job and the grouped gradient kernels at every second dimension
+    class (the tests above cover the others): one job's FSM with a launch per
+    step, in a batch (too many rows for the block kernel) and synchronized."""
+    d = inputs.logreg(n_data=20000 if D <= 64 else 100, dim=D, seed=7)
+    X = torch.tensor(d["X"], dtype=torch.float32, device="cuda")
+    y = torch.tensor(d["y"], dtype=torch.float32, device="cuda")
+    m, n, seed, eps, J = 150, 3, 31, 0.02, 3
+    S, C, _ = gpu_nuts(F, ctx, d, m, n, seed, eps, J, timing=True)
+    S1, C1, _ = gpu_nuts(F, ctx, d, m, n, seed, eps, J, runtime="compact")
+    job = F.Job(ctx, F.logreg_target(X, y), F.nuts_sampler(eps, J), m, n, seed)
+    try:
+        b = F.Batch(ctx, [job], nuts_steps=4)
+        assert b.run(0)
+        b.free()
+        S2, C2 = job.samples(), job.counts()
+    finally:
+        job.free()
+    for s, c in ((S1, C1), (S2, C2)):
+        assert np.array_equal(S, s) and np.array_equal(C, c)
