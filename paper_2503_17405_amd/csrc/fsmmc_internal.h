@@ -121,7 +121,9 @@ hipError_t nuts_block_steps(const JobDev& j, int G, int K, uint32_t step, hipStr
 hipError_t nuts_gradient(const JobDev& j, int mode, uint32_t step, hipStream_t s);  // after nuts_transition(mode, step)
 size_t logreg_split_bytes(const JobDev& j);
 hipError_t logreg_setup(const JobDev& j, hipStream_t s);
-hipError_t nuts_gradient_dense(const JobDev& j, int ncols, float* Gout, float* Uout, int gstride, hipStream_t s);
+// U and the first gcols entries of grad U (NULL: none) at the first ncols positions of Thq.
+hipError_t nuts_gradient_dense(const JobDev& j, int ncols, float* Gout, float* Uout, int gstride, int gcols,
+                               hipStream_t s);
 
 // NUTS on a Gaussian mixture (mog.hip): P (Dp x Dp) in d.prec, means in d.X
 // Setup: P mu_k, the constants, and the persistent launch shape (pwpb, pblocks).

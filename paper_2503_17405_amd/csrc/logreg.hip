@@ -91,12 +91,12 @@ static hipError_t grad_dispatch(const JobDev& j, const GradK& g, hipStream_t s, 
 #undef FSMMC_GRAD_CASE
 }
 
-static hipError_t grad_launch(const JobDev& j, int dense, float* Gout, float* Uout, int gstride, hipStream_t s)
+static hipError_t grad_launch(const JobDev& j, int dense, float* Gout, float* Uout, int gstride, int gcols, hipStream_t s)
 {
     const GradK g = grad_view(j, dense);
     hipError_t e = grad_dispatch(j, g, s, false);
     if (e != hipSuccess) return e;
-    const ReduceK r = reduce_view(j, dense, Gout, Uout, gstride);
+    const ReduceK r = reduce_view(j, dense, Gout, Uout, gstride, gcols);
     const dim3 rg((j.m + 3) / 4);
     if (j.Dp <= 64)
         hipLaunchKernelGGL(logreg_reduce_kernel<1>, rg, dim3(256), 0, s, r);
@@ -131,9 +131,10 @@ hipError_t nuts_gradient(const JobDev& j, int mode, uint32_t step, hipStream_t s
     return grad_dispatch(j, g, s, false);
 }
 
-hipError_t nuts_gradient_dense(const JobDev& j, int ncols, float* Gout, float* Uout, int gstride, hipStream_t s)
+hipError_t nuts_gradient_dense(const JobDev& j, int ncols, float* Gout, float* Uout, int gstride, int gcols,
+                               hipStream_t s)
 {
-    return grad_launch(j, ncols, Gout, Uout, gstride, s);
+    return grad_launch(j, ncols, Gout, Uout, gstride, gcols, s);
 }
 
 }  // namespace fsmmc

@@ -470,9 +470,9 @@ struct ReduceK {
     const int32_t* count;
     const float* Gpart;
     const float* Upart;
-    float* G;  // chain-indexed outputs, row stride gstride
+    float* G;  // chain-indexed outputs, row stride gstride, gcols entries a row (NULL: none)
     float* U;
-    int gstride;
+    int gstride, gcols;
 };
 
 // grad U = theta - sum_s partial_s, U = |theta|^2/2 - sum_s loglik_s (slice order).
@@ -494,7 +494,11 @@ __device__ __forceinline__ void logreg_reduce_one(const ReduceK& a, int p, int l
     }
 #pragma unroll
     for (int e = 0; e < EPL; ++e) g.r[e] = th.r[e] - g.r[e];
-    g.store(a.G + (size_t)c * a.gstride, lane);
+    if (a.G) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e)
+            if (e * 64 + lane < a.gcols) a.G[(size_t)c * a.gstride + e * 64 + lane] = g.r[e];
+    }
     float ll = 0.0f;
     for (int s = 0; s < a.nslices; ++s) ll += a.Upart[(size_t)s * a.m + c];
     const float U = 0.5f * wdot(th, th) - ll;
@@ -524,7 +528,7 @@ inline GradK grad_view(const JobDev& j, int dense)
     return g;
 }
 
-inline ReduceK reduce_view(const JobDev& j, int dense, float* Gout, float* Uout, int gstride)
+inline ReduceK reduce_view(const JobDev& j, int dense, float* Gout, float* Uout, int gstride, int gcols)
 {
     ReduceK r;
     r.m = j.m;
@@ -539,6 +543,7 @@ inline ReduceK reduce_view(const JobDev& j, int dense, float* Gout, float* Uout,
     r.G = Gout;
     r.U = Uout;
     r.gstride = gstride;
+    r.gcols = gcols;
     return r;
 }
 

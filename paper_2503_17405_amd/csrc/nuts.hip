@@ -116,7 +116,7 @@ hipError_t nuts_init_state(const JobDev& j, const void* x0, hipStream_t s)
     }
     // grad U and U at the start, straight into the proposal slots (gP, UP)
     float* gp = (float*)j.V + (size_t)V_GP * j.Dp;
-    return nuts_gradient_dense(j, j.m, gp, (float*)j.lx, vstride, s);
+    return nuts_gradient_dense(j, j.m, gp, (float*)j.lx, vstride, j.Dp, s);
 }
 
 template <int EPL, int NW, bool AHEAD>
