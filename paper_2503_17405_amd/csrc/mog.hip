@@ -45,24 +45,28 @@ struct MogK {
     int D, Dp, K;
 };
 
-// LDS image (in floats): rows k < D of P interleaved per lane ([k][lane][e],
-// so a lane reads its EPL entries of row k in one access), then B [K][Dp]
-// and C [K] as doubles (the P part has an even number of floats).
+// LDS image (doubles): rows k < D of P, and zero rows up to a multiple of eight,
+// interleaved per lane ([k][lane][e], so a
+// lane reads its EPL entries of row k in one access), then B [K][Dp] and C [K].
+// P in FP64 (up to 136 KiB with B and C: one block per CU) because the products
+// are formed there: converting its FP32 entries in the loop was three of a
+// step's eight instructions, and at a quarter of the rate.
+__host__ __device__ inline int mog_rows(int D) { return (D + 7) & ~7; }
 template <int EPL>
-__host__ __device__ inline size_t mog_lds_floats(int D, int Dp, int K)
+__host__ __device__ inline size_t mog_lds_doubles(int D, int Dp, int K)
 {
-    return (size_t)D * 64 * EPL + 2 * ((size_t)K * Dp + (size_t)K);
+    return (size_t)mog_rows(D) * 64 * EPL + (size_t)K * Dp + (size_t)K;
 }
 
 template <int EPL>
-__device__ __forceinline__ void mog_stage(const MogK& mk, float* sm)
+__device__ __forceinline__ void mog_stage(const MogK& mk, double* sm)
 {
-    const int nP = mk.D * 64 * EPL;
+    const int nP = mog_rows(mk.D) * 64 * EPL;  // P is zero padded to Dp rows
     for (int i = threadIdx.x; i < nP; i += blockDim.x) {
         const int k = i / (64 * EPL), r = i - k * 64 * EPL, l = r / EPL, e = r - l * EPL;
-        sm[i] = mk.P[(size_t)k * mk.Dp + e * 64 + l];
+        sm[i] = (double)mk.P[(size_t)k * mk.Dp + e * 64 + l];
     }
-    double* Bs = reinterpret_cast<double*>(sm + nP);
+    double* Bs = sm + nP;
     for (int i = threadIdx.x; i < mk.K * mk.Dp; i += blockDim.x) Bs[i] = mk.B[i];
     double* Cs = Bs + mk.K * mk.Dp;
     for (int i = threadIdx.x; i < mk.K; i += blockDim.x) Cs[i] = mk.C[i];
@@ -71,7 +75,7 @@ __device__ __forceinline__ void mog_stage(const MogK& mk, float* sm)
 
 // Gradient policy of the NUTS step: U and grad U at th, from the LDS image.
 struct MogGrad {
-    const float* P;
+    const double* P;
     const double* B;
     const double* C;
     int D, Dp, K;
@@ -89,14 +93,36 @@ struct MogGrad {
         for (int es = 0; es < EPL; ++es) {
             const int k0 = es * 64;
             const int kn = min(64, D - k0);
-            const int thv = __float_as_int(th.r[es]);
-            const float* pr = P + ((size_t)k0 * 64 + lane) * EPL;
-#pragma unroll 4
-            for (int l = 0; l < kn; ++l) {
-                const double tk = (double)__int_as_float(__builtin_amdgcn_readlane(thv, l));
-                const float* q = pr + (size_t)l * 64 * EPL;
+            const uint64_t thv = __builtin_bit_cast(uint64_t, (double)th.r[es]);
+            const int tlo = (int)(uint32_t)thv, thi = (int)(uint32_t)(thv >> 32);
+            const double* pr = P + ((size_t)k0 * 64 + lane) * EPL;
+            // four rows in flight while the four before them are used (the compiler
+            // does not unroll this loop, and a row at a time waits 90 cycles for
+            // LDS); the rows up to a multiple of eight are zero, as is th there
+            const int kn8 = (kn + 7) & ~7;
+            double qa[4][EPL], qb[4][EPL];
+            auto rows = [&](int l, double (&q)[4][EPL]) {
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) y[e] = fma((double)q[e], tk, y[e]);
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) q[i][e] = pr[(size_t)(l + i) * 64 * EPL + e];
+            };
+            auto add = [&](int l, const double (&q)[4][EPL]) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double tk = __builtin_bit_cast(
+                        double, (uint64_t)(uint32_t)__builtin_amdgcn_readlane(tlo, l + i) |
+                                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane(thi, l + i) << 32);
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) y[e] = fma(q[i][e], tk, y[e]);
+                }
+            };
+            rows(0, qa);
+            for (int l = 0; l < kn8; l += 8) {
+                rows(l + 4, qb);
+                add(l, qa);
+                rows(min(l + 8, kn8 - 4), qa);
+                add(l + 4, qb);
             }
         }
         // s_0 = th . y and s_k = b_k . th, lane-local then one butterfly each
@@ -142,9 +168,9 @@ struct MogGrad {
 };
 
 template <int EPL>
-__device__ __forceinline__ MogGrad mog_policy(const MogK& mk, const float* sm)
+__device__ __forceinline__ MogGrad mog_policy(const MogK& mk, const double* sm)
 {
-    const double* Bs = reinterpret_cast<const double*>(sm + (size_t)mk.D * 64 * EPL);
+    const double* Bs = sm + (size_t)mog_rows(mk.D) * 64 * EPL;
     return MogGrad{sm, Bs, Bs + (size_t)mk.K * mk.Dp, mk.D, mk.Dp, mk.K};
 }
 
@@ -168,7 +194,7 @@ template <int EPL>
 __global__ __launch_bounds__(512) void nuts_mog_kernel(NutsK a, MogK mk, unsigned long long* q,
                                                       unsigned long long base, int sync)
 {
-    extern __shared__ float sm[];
+    extern __shared__ __align__(16) double sm[];
     mog_stage<EPL>(mk, sm);
     const MogGrad G = mog_policy<EPL>(mk, sm);
     const int lane = threadIdx.x & 63;
@@ -199,7 +225,7 @@ template <int EPL>
 __global__ __launch_bounds__(512) void nuts_mog_pad_kernel(NutsK a, MogK mk, unsigned long long* q,
                                                           unsigned long long base, uint32_t draw, float* sink)
 {
-    extern __shared__ float sm[];
+    extern __shared__ __align__(16) double sm[];
     mog_stage<EPL>(mk, sm);
     const MogGrad G = mog_policy<EPL>(mk, sm);
     const int lane = threadIdx.x & 63;
@@ -230,7 +256,7 @@ template <int EPL>
 __global__ __launch_bounds__(512) void mog_eval_kernel(MogK mk, const float* pts, int ldp, int n, float* Gout,
                                                       int ldg, int gcols, float* Uout, int ldu)
 {
-    extern __shared__ float sm[];
+    extern __shared__ __align__(16) double sm[];
     mog_stage<EPL>(mk, sm);
     const MogGrad G = mog_policy<EPL>(mk, sm);
     const int lane = threadIdx.x & 63;
@@ -295,20 +321,21 @@ static MogK mog_view(const JobDev& j)
 
 static size_t mog_lds_bytes(const JobDev& j)
 {
-    return 4 * (j.EPL == 1 ? mog_lds_floats<1>(j.D, j.Dp, j.K) : mog_lds_floats<2>(j.D, j.Dp, j.K));
+    return 8 * (j.EPL == 1 ? mog_lds_doubles<1>(j.D, j.Dp, j.K) : mog_lds_doubles<2>(j.D, j.Dp, j.K));
 }
 
 // Launch shape of the persistent kernels: waves per block grow with the
-// chain count (one wave per block for small jobs, so chains spread over the
-// CUs; 8 per block when the chip is full), blocks capped at what the chip
+// chain count (as few as spread the chains over the CUs, one or two blocks on
+// each; 8 per block when the chip is full), blocks capped at what the chip
 // holds at once (LDS bound).
 static void mog_shape(JobDev& j)
 {
-    const int w = std::min(8, std::max(1, (j.m + 511) / 512));
-    const int need = (j.m + w - 1) / w;
     const size_t lds = mog_lds_bytes(j);
     int per_cu = (int)std::min<size_t>(8, (160 * 1024) / std::max<size_t>(lds, 1));
     per_cu = std::max(per_cu, 1);
+    const int spread = 256 * std::min(per_cu, 2);
+    const int w = std::min(8, std::max(1, (j.m + spread - 1) / spread));
+    const int need = (j.m + w - 1) / w;
     int cus = 256, dev = 0;
     if (hipGetDevice(&dev) == hipSuccess) {
         int v = 0;
