@@ -73,6 +73,14 @@ __device__ __forceinline__ void mog_stage(const MogK& mk, double* sm)
     __syncthreads();
 }
 
+// Lane l's value (l wave-uniform).
+__device__ __forceinline__ double lane_value(double v, int l)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l) |
+                                          (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l) << 32);
+}
+
 // Gradient policy of the NUTS step: U and grad U at th, from the LDS image.
 struct MogGrad {
     const double* P;
@@ -93,8 +101,7 @@ struct MogGrad {
         for (int es = 0; es < EPL; ++es) {
             const int k0 = es * 64;
             const int kn = min(64, D - k0);
-            const uint64_t thv = __builtin_bit_cast(uint64_t, (double)th.r[es]);
-            const int tlo = (int)(uint32_t)thv, thi = (int)(uint32_t)(thv >> 32);
+            const double thv = (double)th.r[es];
             const double* pr = P + ((size_t)k0 * 64 + lane) * EPL;
             // four rows in flight while the four before them are used (the compiler
             // does not unroll this loop, and a row at a time waits 90 cycles for
@@ -110,9 +117,7 @@ struct MogGrad {
             auto add = [&](int l, const double (&q)[4][EPL]) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const double tk = __builtin_bit_cast(
-                        double, (uint64_t)(uint32_t)__builtin_amdgcn_readlane(tlo, l + i) |
-                                    (uint64_t)(uint32_t)__builtin_amdgcn_readlane(thi, l + i) << 32);
+                    const double tk = lane_value(thv, l + i);
 #pragma unroll
                     for (int e = 0; e < EPL; ++e) y[e] = fma(q[i][e], tk, y[e]);
                 }
@@ -137,27 +142,42 @@ struct MogGrad {
                 for (int e = 0; e < EPL; ++e) pk[kc] += B[kc * Dp + e * 64 + lane] * (double)th.r[e];
             }
         }
-        const double s0 = uni(wave_sum(p0));
-        double ak[kMogMaxK];
+        // the sums of up to four components (and s_0) go through their butterflies
+        // side by side; the exponentials of all components are one evaluation,
+        // component k in lane k (their sum keeps the order of k)
+        double s0 = 0.0, ak[kMogMaxK], av = 0.0;
         double amax = -INFINITY;
 #pragma unroll
-        for (int kc = 0; kc < kMogMaxK; ++kc) {
-            if (kc < K) {
-                const double sk = uni(wave_sum(pk[kc]));
-                ak[kc] = (C[kc] - 0.5 * s0) + sk;
-                amax = fmax(amax, ak[kc]);
+        for (int kg = 0; kg < kMogMaxK; kg += 4) {
+            if (kg < K) {
+                double sk[4];
+                if (kg == 0) s0 = wave_sum(p0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sk[i] = wave_sum(pk[kg + i]);
+                if (kg == 0) s0 = uni(s0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int kc = kg + i;
+                    if (kc < K) {
+                        ak[kc] = (C[kc] - 0.5 * s0) + uni(sk[i]);
+                        amax = fmax(amax, ak[kc]);
+                        av = lane == kc ? ak[kc] : av;
+                    }
+                }
             }
         }
+        const double ev = exp(av - amax);
         double z = 0.0;
 #pragma unroll
         for (int kc = 0; kc < kMogMaxK; ++kc)
-            if (kc < K) z += exp(ak[kc] - amax);
+            if (kc < K) z += lane_value(ev, kc);
         const double lse = amax + log(z);
         U = (float)(-lse);
+        const double rv = exp(av - lse);
 #pragma unroll
         for (int kc = 0; kc < kMogMaxK; ++kc) {
             if (kc < K) {
-                const double r = exp(ak[kc] - lse);
+                const double r = lane_value(rv, kc);
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) y[e] -= r * B[kc * Dp + e * 64 + lane];
             }
