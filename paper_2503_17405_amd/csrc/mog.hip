@@ -11,7 +11,7 @@
 // inside the step instead of by a separate batched launch: the NUTS FSM step
 // (nuts_chain_body, shared with the logistic-regression path) runs with a
 // gradient policy that evaluates
-//   y = P x (P staged in LDS, x broadcast lane by lane from registers),
+//   y = P x (P and x staged in LDS in FP64),
 //   s_0 = x . y,  s_k = (P mu_k) . x,
 //   a_k = (log w_k - mu_k^T P mu_k / 2) - s_0 / 2 + s_k,
 //   U = -logsumexp_k a_k,  grad U = y - sum_k e^(a_k + U) P mu_k.
@@ -46,16 +46,16 @@ struct MogK {
 };
 
 // LDS image (doubles): rows k < D of P, and zero rows up to a multiple of eight,
-// interleaved per lane ([k][lane][e], so a
-// lane reads its EPL entries of row k in one access), then B [K][Dp] and C [K].
-// P in FP64 (up to 136 KiB with B and C: one block per CU) because the products
-// are formed there: converting its FP32 entries in the loop was three of a
-// step's eight instructions, and at a quarter of the rate.
+// interleaved per lane ([k][lane][e], so a lane reads its EPL entries of row k in
+// one access), then B [K][Dp], C [K] and a position per wave.  P in FP64 (with the
+// rest up to 144 KiB: one block per CU) because the products are formed there:
+// converting its entries in the loop was three of a row's eight instructions,
+// and at a quarter of the rate.
 __host__ __device__ inline int mog_rows(int D) { return (D + 7) & ~7; }
 template <int EPL>
 __host__ __device__ inline size_t mog_lds_doubles(int D, int Dp, int K)
 {
-    return (size_t)mog_rows(D) * 64 * EPL + (size_t)K * Dp + (size_t)K;
+    return (size_t)mog_rows(D) * 64 * EPL + (size_t)K * Dp + (size_t)((K + 1) & ~1) + 8 * 64 * EPL;
 }
 
 template <int EPL>
@@ -83,6 +83,7 @@ __device__ __forceinline__ double lane_value(double v, int l)
 
 // Gradient policy of the NUTS step: U and grad U at th, from the LDS image.
 struct MogGrad {
+    double* T;  // the wave's position in FP64
     const double* P;
     const double* B;
     const double* C;
@@ -95,39 +96,43 @@ struct MogGrad {
         double y[EPL];
 #pragma unroll
         for (int e = 0; e < EPL; ++e) y[e] = 0.0;
-        // y = P th: row k of P times th_k, k ascending; th_k read from lane k & 63
-        // of register e = k / 64 (a scalar broadcast, no LDS traffic)
+        // y = P th: row k of P times th_k, k ascending; th_k, in FP64, comes from LDS
+        // (one address for all lanes: two of them in a read; from another lane's
+        // register it took two v_readlane and the wait for their scalars, 50 cycles
+        // a row instead of 30: 500 chains x 200 draws at D = 100 13.7 -> 11.0 ms)
 #pragma unroll
         for (int es = 0; es < EPL; ++es) {
             const int k0 = es * 64;
             const int kn = min(64, D - k0);
-            const double thv = (double)th.r[es];
+            T[es * 64 + lane] = (double)th.r[es];
+            __builtin_amdgcn_wave_barrier();  // read by the other lanes of the wave
             const double* pr = P + ((size_t)k0 * 64 + lane) * EPL;
             // four rows in flight while the four before them are used (the compiler
             // does not unroll this loop, and a row at a time waits 90 cycles for
             // LDS); the rows up to a multiple of eight are zero, as is th there
             const int kn8 = (kn + 7) & ~7;
-            double qa[4][EPL], qb[4][EPL];
-            auto rows = [&](int l, double (&q)[4][EPL]) {
+            double qa[4][EPL], qb[4][EPL], ta[4], tb[4];
+            auto rows = [&](int l, double (&q)[4][EPL], double (&t)[4]) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t[i] = T[k0 + l + i];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int e = 0; e < EPL; ++e) q[i][e] = pr[(size_t)(l + i) * 64 * EPL + e];
             };
-            auto add = [&](int l, const double (&q)[4][EPL]) {
+            auto add = [&](const double (&q)[4][EPL], const double (&t)[4]) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const double tk = lane_value(thv, l + i);
 #pragma unroll
-                    for (int e = 0; e < EPL; ++e) y[e] = fma(q[i][e], tk, y[e]);
+                    for (int e = 0; e < EPL; ++e) y[e] = fma(q[i][e], t[i], y[e]);
                 }
             };
-            rows(0, qa);
+            rows(0, qa, ta);
             for (int l = 0; l < kn8; l += 8) {
-                rows(l + 4, qb);
-                add(l, qa);
-                rows(min(l + 8, kn8 - 4), qa);
-                add(l + 4, qb);
+                rows(l + 4, qb, tb);
+                add(qa, ta);
+                rows(min(l + 8, kn8 - 4), qa, ta);
+                add(qb, tb);
             }
         }
         // s_0 = th . y and s_k = b_k . th, lane-local then one butterfly each
@@ -188,10 +193,12 @@ struct MogGrad {
 };
 
 template <int EPL>
-__device__ __forceinline__ MogGrad mog_policy(const MogK& mk, const double* sm)
+__device__ __forceinline__ MogGrad mog_policy(const MogK& mk, double* sm)
 {
     const double* Bs = sm + (size_t)mog_rows(mk.D) * 64 * EPL;
-    return MogGrad{sm, Bs, Bs + (size_t)mk.K * mk.Dp, mk.D, mk.Dp, mk.K};
+    double* T = sm + (size_t)mog_rows(mk.D) * 64 * EPL + (size_t)mk.K * mk.Dp + ((mk.K + 1) & ~1) +
+                (threadIdx.x >> 6) * 64 * EPL;
+    return MogGrad{T, sm, Bs, Bs + (size_t)mk.K * mk.Dp, mk.D, mk.Dp, mk.K};
 }
 
 // Next chain of a persistent kernel: tickets count up across launches; this

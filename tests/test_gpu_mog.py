@@ -170,3 +170,40 @@ def test_mog_argument_errors(F, ctx):
         assert e.value.status == F.ENOTSUP
     finally:
         job.free()
+
+
+# rows of P that end inside a group of eight, one and two registers a lane, one to
+# eight components (groups of four), the largest LDS image; FP64 sums rounded to
+# FP32 once: 2^-22 of the terms' size
+@pytest.mark.parametrize("D,K", [(1, 1), (7, 4), (8, 5), (9, 8), (63, 3), (65, 2), (71, 4), (121, 5), (128, 8)])
+def test_mog_row_and_component_edges(F, ctx, D, K):
+    rng = np.random.default_rng(100 * D + K)
+    A = rng.standard_normal((D, D)) / np.sqrt(D)
+    P = (A @ A.T + np.eye(D)).astype(np.float32)
+    P = np.tril(P) + np.tril(P, -1).T
+    w = dict(means=rng.standard_normal((K, D)).astype(np.float32),
+             log_weights=np.log(rng.dirichlet(np.ones(K))).astype(np.float32), prec=P)
+    m = 11
+    pts = rng.standard_normal((m, D)).astype(np.float32)
+    job = mog_job(F, ctx, w, m, 1, 1, 0.05, 4)
+    try:
+        U, g = job.potential(torch.tensor(pts, device="cuda"))
+        U, g = U.cpu().numpy().astype(np.float64), g.cpu().numpy().astype(np.float64)
+    finally:
+        job.free()
+    tg = oracle_target(w)
+    for i in range(m):
+        Ur, gr = O.potential(tg, pts[i].astype(np.float64), grad=True)
+        size = (np.abs(P.astype(np.float64)) @ (np.abs(pts[i]) + np.abs(w["means"]).max(0))).max()
+        assert np.max(np.abs(g[i] - gr)) <= 2.0 ** -22 * (1.0 + size)
+        assert abs(U[i] - Ur) <= 2.0 ** -22 * (1.0 + abs(Ur))
+
+
+@pytest.mark.parametrize("m", [255, 257, 1030, 2049])
+def test_mog_waves_per_block(F, ctx, m):
+    """One to eight waves per block (chains over 256 blocks, then over several
+    rounds): the draws of the synchronized runtime."""
+    w = inputs.mog(dim=90, n_chains=m, seed=5)
+    S, C, _ = run(F, ctx, w, m, 3, 9, 0.05, 4, x0=w["x0"])
+    S1, C1, _ = run(F, ctx, w, m, 3, 9, 0.05, 4, x0=w["x0"], runtime="vmap")
+    assert np.array_equal(S, S1) and np.array_equal(C, C1)
