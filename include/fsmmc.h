@@ -128,7 +128,8 @@ typedef struct {
 typedef struct {
     int32_t window;        /* ESS: draws of ellipse directions precomputed per chain */
     int32_t timing;        /* 1: time every kernel launch with HIP events on the job's
-                              stream (reported by fsmmc_job_stats)                   */
+                              stream (reported by fsmmc_job_stats); NUTS on LOGREG then
+                              runs a launch per step and per gradient               */
     int32_t fsm_states;    /* DRSYM: 0 or 1 = condensed FSM (the loop body is one state,
                               one try per step); 4 = the loop body split into four
                               states PROPOSE, EVAL, TEST, NEXT, one per step (Sec.
@@ -272,8 +273,8 @@ fsmmc_status fsmmc_eval_potential(fsmmc_job* job, int32_t n_points, const void* 
 /* fsmmc_eval_potential for callers that cannot allocate device memory (code
  * under stream or graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): the same kernels and the same bits, but the padded results go
- * through the library's fixed per-device workspace instead of buffers
- * allocated per call, and the call does not synchronise.
+ * through the library's fixed per-device workspace, memory that kernels cannot
+ * reach is not copied, and the call does not synchronise.
  *   theta: device, n_points x dim positions (n_points <= n_chains);
  *   grad:  device, n_points x dim output, or NULL;
  *   U:     device, n_points output.
