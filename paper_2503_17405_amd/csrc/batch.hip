@@ -360,19 +360,6 @@ fsmmc_status upload(T* dst, const std::vector<T>& v)
         if (s__ != FSMMC_OK) return s__;       \
     } while (0)
 
-// The nodes the next launch captured on s would follow.
-hipError_t capture_tail(hipStream_t s, std::vector<hipGraphNode_t>& nodes)
-{
-    hipStreamCaptureStatus st;
-    unsigned long long id;
-    hipGraph_t g;
-    const hipGraphNode_t* deps = nullptr;
-    size_t n = 0;
-    const hipError_t e = hipStreamGetCaptureInfo_v2(s, &st, &id, &g, &deps, &n);
-    if (e == hipSuccess) nodes.assign(deps, deps + n);
-    return e;
-}
-
 // Rebuild the job views and work tables for the live jobs and the current
 // configuration, then capture the round graph.
 fsmmc_status rebuild(fsmmc_batch* b)
@@ -497,12 +484,17 @@ fsmmc_status rebuild(fsmmc_batch* b)
     };
     hipLaunchKernelGGL(batch_begin_kernel, dim3(1), dim3(256), 0, s, h, jobs, (const int32_t*)b->d_njobs, b->n_nuts);
     chk();
-    // The NUTS steps are a branch of their own beside the GEMM and the FSM queue: they
-    // leave compute units idle (one block per CU at most, or waves that wait for
-    // memory), and the queue takes up whatever they leave.
-    std::vector<hipGraphNode_t> begin, nuts_end;
-    const bool fork = b->n_items > 0 && b->nuts_steps > 0 && b->nblock_cnt + b->n_nuts > 0;
-    if (e == hipSuccess && fork) e = capture_tail(s, begin);
+    for (int t = 0; t < kTileSlots && e == hipSuccess; ++t)
+        if (b->tile_cnt[t] > 0) e = launch_tiles(t, b->tile_cnt[t], jobs, b->d_tiles + b->tile_off[t], s);
+    if (e == hipSuccess && b->n_items > 0) {
+        if (b->wide)
+            hipLaunchKernelGGL(batch_fsm_kernel<true>, dim3(b->fsm_blocks), dim3(256), 0, s, jobs,
+                               (const BItem*)b->d_items, b->n_items, h);
+        else
+            hipLaunchKernelGGL(batch_fsm_kernel<false>, dim3(b->fsm_blocks), dim3(256), 0, s, jobs,
+                               (const BItem*)b->d_items, b->n_items, h);
+        chk();
+    }
     if (e == hipSuccess && b->nblock_cnt > 0 && b->nuts_steps > 0) {
         hipLaunchKernelGGL(batch_nuts_block_kernel, dim3(b->nblock_cnt), dim3(64 * kNutsBlockWaves), b->nblock_lds, s,
                            jobs, (const BItem*)b->d_nitems + b->nstep_cnt[0] + b->nstep_cnt[1], b->nuts_steps);
@@ -525,22 +517,6 @@ fsmmc_status rebuild(fsmmc_batch* b)
                                (const BGrad*)b->d_grads + b->grad_cnt[0], slot);
         chk();
     }
-    if (e == hipSuccess && fork) e = capture_tail(s, nuts_end);
-    if (e == hipSuccess && fork)
-        e = hipStreamUpdateCaptureDependencies(s, begin.data(), begin.size(), hipStreamSetCaptureDependencies);
-    for (int t = 0; t < kTileSlots && e == hipSuccess; ++t)
-        if (b->tile_cnt[t] > 0) e = launch_tiles(t, b->tile_cnt[t], jobs, b->d_tiles + b->tile_off[t], s);
-    if (e == hipSuccess && b->n_items > 0) {
-        if (b->wide)
-            hipLaunchKernelGGL(batch_fsm_kernel<true>, dim3(b->fsm_blocks), dim3(256), 0, s, jobs,
-                               (const BItem*)b->d_items, b->n_items, h);
-        else
-            hipLaunchKernelGGL(batch_fsm_kernel<false>, dim3(b->fsm_blocks), dim3(256), 0, s, jobs,
-                               (const BItem*)b->d_items, b->n_items, h);
-        chk();
-    }
-    if (e == hipSuccess && fork)
-        e = hipStreamUpdateCaptureDependencies(s, nuts_end.data(), nuts_end.size(), hipStreamAddCaptureDependencies);
     if (e == hipSuccess && nj > 0) {
         hipLaunchKernelGGL(batch_tally_kernel, dim3(nj), dim3(256), 0, s, h, jobs, js);
         chk();
