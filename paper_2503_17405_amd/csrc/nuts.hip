@@ -127,9 +127,10 @@ static void fsm_step_launch(const NutsK& a, hipStream_t s)
 
 // Four chains per block up to 1024 chains (every block has a CU to itself),
 // eight above, where the blocks' atomics on the one count cost more than the
-// wait for a block's slowest chain.  Vectors ahead up to 2048 chains: D = 20, 16
-// chains, 100 draws 33.0 -> 24.6 ms; D = 20, 2048 chains, 25 draws 10.4 -> 9.5;
-// at 65536 chains the extra reads cost 16.0 -> 16.6, at D = 100 42.2 -> 50.2.
+// wait for a block's slowest chain.  Vectors and 32 slices ahead up to 2048
+// chains: 46 chains, N = 8000, D = 50 (250 slices) 6.0 -> 4.8 ms, N = 5379, D = 83
+// (169 slices) 47 -> 40 ms; at 65536 chains the vectors' extra reads cost 16.0 ->
+// 16.6 ms at D = 20, 42.2 -> 50.2 at D = 100.
 template <int EPL>
 static void fsm_step(const NutsK& a, hipStream_t s)
 {
