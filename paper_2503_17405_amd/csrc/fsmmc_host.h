@@ -18,13 +18,11 @@ struct fsmmc_ctx {
     size_t budget = 0;
     std::atomic<size_t> used{0};
     std::atomic<int> jobs{0};
-    // Handed from freed jobs to new ones (creating them costs more than a small
-    // job): side streams with nothing queued, and the slots of one pinned page.
-    // Released with the context, which outlives its jobs.
-    static constexpr size_t kIdleStreams = 8;
+    // One page of pinned words, its slots handed from freed jobs to new ones (an
+    // allocation of each costs more than a small job's kernels).  Released with
+    // the context, which outlives its jobs.
     static constexpr int kPinnedSlots = 32;  // of 16 64-bit words
     std::mutex mu;
-    std::vector<hipStream_t> idle_streams;
     unsigned long long* pinned = nullptr;
     uint32_t pinned_free = 0;  // bit i: slot i is free
 };

@@ -265,7 +265,7 @@ def test_ess_argument_errors(F, ctx):
 
 
 def test_ess_many_jobs_share_a_context(F):
-    """More live jobs than the context keeps pinned slots and side streams for,
+    """More live jobs than the context keeps pinned slots for,
     stepped and freed from several threads, in two waves: the draws of a job
     on its own.  chol_L with entries above the diagonal, which are not read."""
     import threading
