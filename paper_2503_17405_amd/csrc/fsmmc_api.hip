@@ -142,7 +142,51 @@ static fsmmc_status scratch_setup(int device, void** out)
     return FSMMC_OK;
 }
 
-// Device memory of a job.  zero: cleared.  Small arrays are cut from zeroed slabs:
+// Idle buffers back to the device (an allocation that fails is tried again after).
+static void idle_release(fsmmc_ctx* c)
+{
+    std::lock_guard<std::mutex> lk(c->mu);
+    for (const fsmmc_ctx::Idle& b : c->idle) (void)hipFree(b.p);
+    c->idle.clear();
+    c->idle_bytes = 0;
+}
+
+// An idle buffer of at least `bytes` and at most a quarter more, or NULL.
+static void* idle_take(fsmmc_ctx* c, size_t bytes, size_t* got)
+{
+    std::lock_guard<std::mutex> lk(c->mu);
+    for (size_t i = 0; i < c->idle.size(); ++i) {
+        const fsmmc_ctx::Idle b = c->idle[i];
+        if (b.bytes < bytes || b.bytes > bytes + bytes / 4) continue;
+        c->idle.erase(c->idle.begin() + i);
+        c->idle_bytes -= b.bytes;
+        *got = b.bytes;
+        return b.p;
+    }
+    return nullptr;
+}
+
+// Keeps an unused buffer if there is room (nothing on the device may use it any more).
+static bool idle_give(fsmmc_ctx* c, void* p, size_t bytes)
+{
+    if (c->budget) return false;
+    std::lock_guard<std::mutex> lk(c->mu);
+    if (c->idle_bytes + bytes > fsmmc_ctx::kIdleBytes) return false;
+    c->idle.push_back({p, bytes});
+    c->idle_bytes += bytes;
+    return true;
+}
+
+static hipError_t device_malloc(fsmmc_ctx* c, void** p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    idle_release(c);
+    return hipMalloc(p, bytes);
+}
+
+// Device memory of a job.  zero: cleared, else a job's one direction buffer.  Small arrays are cut from zeroed slabs:
 // a job has about twenty, and an allocation, a clear and a free of each were a
 // third of a millisecond.  The budget counts what was asked for.
 static fsmmc_status job_alloc(fsmmc_job* j, size_t bytes, void** p, bool zero = true)
@@ -163,7 +207,7 @@ static fsmmc_status job_alloc(fsmmc_job* j, size_t bytes, void** p, bool zero = 
     const size_t slab = std::min<size_t>(8u << 20, std::max<size_t>(256u << 10, (size_t)j->d.m * 128));
     const size_t cut = (bytes + 255) & ~(size_t)255;
     hipError_t e = hipSuccess;
-    if (cut <= slab / 4) {
+    if (zero && cut <= slab / 4) {
         if (j->slab_left < cut) {
             void* q = nullptr;
             if (hipMalloc(&q, slab) == hipSuccess) {
@@ -181,15 +225,26 @@ static fsmmc_status job_alloc(fsmmc_job* j, size_t bytes, void** p, bool zero = 
             j->slab_left -= cut;
         }
     }
-    if (!*p) {
-        e = hipMalloc(p, bytes);
+    if (!*p && !zero) {
+        size_t got = bytes;
+        *p = c->budget ? nullptr : idle_take(c, bytes, &got);
+        if (!*p) e = device_malloc(c, p, bytes);
+        if (e != hipSuccess) {
+            c->used.fetch_sub(bytes);
+            *p = nullptr;
+            return fail(FSMMC_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+        }
+        j->dirs = *p;
+        j->dirs_bytes = got;
+    } else if (!*p) {
+        e = device_malloc(c, p, bytes);
         if (e != hipSuccess) {
             c->used.fetch_sub(bytes);
             *p = nullptr;
             return fail(FSMMC_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
         }
         j->allocs.push_back(*p);
-        if (zero) e = hipMemsetAsync(*p, 0, bytes, j->stream);
+        e = hipMemsetAsync(*p, 0, bytes, j->stream);
     }
     j->bytes += bytes;
     if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
@@ -257,6 +312,8 @@ static void job_release(fsmmc_job* j)
         (void)hipStreamSynchronize(j->side);
         (void)hipStreamDestroy(j->side);
     }
+    if (j->dirs && !(hipDeviceSynchronize() == hipSuccess && idle_give(j->ctx, j->dirs, j->dirs_bytes)))
+        (void)hipFree(j->dirs);
     for (void* p : j->allocs) (void)hipFree(p);
     pinned_give(j);
     for (const TimedLaunch& t : j->pending) {
@@ -321,6 +378,7 @@ fsmmc_status fsmmc_ctx_destroy(fsmmc_ctx* ctx)
 {
     if (!ctx) return fail(FSMMC_EINVAL, "ctx is NULL");
     if (ctx->jobs.load() != 0) return fail(FSMMC_EBUSY, "context still has jobs");
+    idle_release(ctx);
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     delete ctx;
     return FSMMC_OK;

@@ -22,6 +22,16 @@ struct fsmmc_ctx {
     // allocation of each costs more than a small job's kernels).  Released with
     // the context, which outlives its jobs.
     static constexpr int kPinnedSlots = 32;  // of 16 64-bit words
+    // Direction buffers of freed jobs, at most kIdleBytes, for the next jobs of a
+    // context without a budget: freeing and allocating hundreds of MiB every few
+    // milliseconds stalls in the driver (a batch of 8 ms took 19 to 60).
+    static constexpr size_t kIdleBytes = (size_t)1 << 30;
+    struct Idle {
+        void* p;
+        size_t bytes;
+    };
+    std::vector<Idle> idle;
+    size_t idle_bytes = 0;
     std::mutex mu;
     unsigned long long* pinned = nullptr;
     uint32_t pinned_free = 0;  // bit i: slot i is free
@@ -61,6 +71,8 @@ struct fsmmc_job {
     fsmmc::JobDev d;
     std::vector<void*> allocs;
     size_t bytes = 0;
+    void* dirs = nullptr;  // the direction buffer (kept by the context when the job is freed)
+    size_t dirs_bytes = 0;
     unsigned char* slab = nullptr;  // zeroed memory not handed out yet (job_alloc)
     size_t slab_left = 0;
     unsigned long long* h_ctr = nullptr;  // pinned: [0..7] mirror of d.ctr, [8..15] scratch reads
