@@ -261,6 +261,9 @@ fsmmc_status fsmmc_collect_counts(fsmmc_job* job, int32_t* dst);
  *   grad:  device, n_points x dim output, or NULL;
  *   U:     device, n_points output.
  * Uses the job's scratch buffers: call it only between stepping calls.
+ * Leapfrogs that a batch freed in mid-run left waiting for their gradient
+ * are finished first, as the next stepping call would (a chain may complete
+ * its draw by that).
  * Synchronises the job's stream.  Errors: EINVAL, ENOTSUP (ESS jobs). */
 fsmmc_status fsmmc_eval_potential(fsmmc_job* job, int32_t n_points, const void* theta, void* grad,
                                   void* U);
@@ -285,9 +288,10 @@ fsmmc_status fsmmc_eval_potential(fsmmc_job* job, int32_t n_points, const void* 
  * EINVAL.  Every call on one GPU shares the workspace (and uses the job's
  * request and partial buffers, like fsmmc_eval_potential), so calls that may
  * overlap on one GPU -- other streams, other threads -- race and must be
- * ordered by the caller.  Nothing in the workspace needs to start at zero:
- * each call writes every entry it reads.  Errors: EINVAL, ENOTSUP (not a
- * NUTS job), EBUSY (job in a batch or server), EDEVICE. */
+ * ordered by the caller.  A graph captured from this call is replayed only
+ * while no batch has stepped the job since.  Nothing in the workspace needs to
+ * start at zero: each call writes every entry it reads.  Errors: EINVAL,
+ * ENOTSUP (not a NUTS job), EBUSY (job in a batch or server), EDEVICE. */
 fsmmc_status fsmmc_eval_potential_noalloc(fsmmc_job* job, int32_t n_points, const void* theta,
                                           void* grad, void* U);
 

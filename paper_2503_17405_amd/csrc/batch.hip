@@ -633,6 +633,7 @@ void batch_remove(fsmmc_batch* b, fsmmc_job* j)
     (void)hipStreamSynchronize(b->stream);
     for (size_t i = 0; i < b->jobs.size(); ++i) {
         if (b->jobs[i] != j) continue;
+        if (j->d.kind == FSMMC_NUTS && b->live[i]) j->waiting = true;
         b->jobs.erase(b->jobs.begin() + i);
         b->live.erase(b->live.begin() + i);
         b->had_items.erase(b->had_items.begin() + i);

@@ -787,6 +787,7 @@ static fsmmc_status nuts_run(fsmmc_job* job, int mode, int64_t max_steps, uint32
 {
     JobDev& d = job->d;
     d.tstop = tstop;
+    if (mode == 0) job->waiting = false;
     const int64_t b = max_steps > 0 ? max_steps : INT64_MAX;
     hipLaunchKernelGGL(fill_i64_kernel, dim3((d.m + 255) / 256), dim3(256), 0, job->stream, d.budget, b, d.m);
     HIP_TRY(hipGetLastError());
@@ -1244,11 +1245,12 @@ fsmmc_status fsmmc_eval_potential(fsmmc_job* job, int32_t n_points, const void* 
         HIP_TRY(hipStreamSynchronize(job->stream));
         return FSMMC_OK;
     }
-    // The positions go through the request buffer, which only the gradient
-    // kernels read; the sums over the row slices go straight to the caller's
-    // buffers.  (Two allocations, a clear and three copies beside the kernels were
-    // 50 of a call's 170 us at 4096 points, N = 10^4, D = 100.)  Memory that kernels
-    // cannot reach is copied.
+    // The positions go through the request buffer and the slices' partial sums, which
+    // hold a chain's state while its leapfrog waits for the gradient (so nuts_settle
+    // first); the sums over the slices go straight to the caller's buffers.  (Two
+    // allocations, a clear and three copies beside the kernels were 50 of a call's 170
+    // us at 4096 points, N = 10^4, D = 100.)  Memory that kernels cannot reach is
+    // copied.
     const size_t bt = (size_t)n_points * d.D * 4, bu = (size_t)n_points * 4, np = (size_t)n_points * d.Dp;
     unsigned char* tmp = nullptr;
     if (!kernel_reaches(theta) || !kernel_reaches(U) || (grad && !kernel_reaches(grad))) {
@@ -1258,6 +1260,7 @@ fsmmc_status fsmmc_eval_potential(fsmmc_job* job, int32_t n_points, const void* 
     float* g = tmp && grad ? (float*)(tmp + bt) : (float*)grad;
     float* u = tmp ? (float*)(tmp + 2 * bt) : (float*)U;
     hipError_t e = tmp ? hipMemcpyAsync(tmp, theta, bt, hipMemcpyDefault, job->stream) : hipSuccess;
+    if (e == hipSuccess && job->waiting) e = nuts_settle(d, job->stream);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(pack_points_kernel, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, job->stream, th,
                            (float*)d.Thq, n_points, d.D, d.Dp);
@@ -1269,6 +1272,7 @@ fsmmc_status fsmmc_eval_potential(fsmmc_job* job, int32_t n_points, const void* 
     if (e == hipSuccess) e = hipStreamSynchronize(job->stream);
     if (tmp) (void)hipFree(tmp);
     if (e != hipSuccess) return hip_fail(e, "fsmmc_eval_potential");
+    job->waiting = false;
     return FSMMC_OK;
 }
 
@@ -1296,6 +1300,8 @@ fsmmc_status fsmmc_eval_potential_noalloc(fsmmc_job* job, int32_t n_points, cons
     float* tg = static_cast<float*>(base);
     float* tu = reinterpret_cast<float*>(static_cast<unsigned char*>(base) + gbytes);
     const size_t np = (size_t)n_points * d.Dp;
+    // the flag stays: under capture nothing has run yet
+    if (job->waiting) HIP_TRY(nuts_settle(d, job->stream));
     hipLaunchKernelGGL(pack_points_kernel, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, job->stream,
                        (const float*)theta, (float*)d.Thq, n_points, d.D, d.Dp);
     HIP_TRY(hipGetLastError());

@@ -78,6 +78,9 @@ struct fsmmc_job {
     unsigned long long* h_ctr = nullptr;  // pinned: [0..7] mirror of d.ctr, [8..15] scratch reads
     int launches = 0;
     uint32_t step = 0;  // NUTS runtime step counter (keys the per-step counters)
+    // NUTS on LOGREG: a batch may have left leapfrogs waiting for their gradient, so
+    // Thq, Gpart and Upart hold state (the job's own step calls leave none)
+    bool waiting = false;
     uint32_t t_lo = 0;  // every chain holds at least t_lo draws (known without reading the device)
     unsigned long long qticket = 0;  // NUTS on a mixture: chain-queue base of the next launch
     fsmmc_batch* batch = nullptr;  // the batch or server that owns the job's stepping, if any

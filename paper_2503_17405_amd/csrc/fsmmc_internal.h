@@ -118,6 +118,7 @@ hipError_t nuts_transition(const JobDev& j, int mode, uint32_t step, hipStream_t
 int nuts_block_chains(const JobDev& j, int64_t chains);  // chains: of the jobs that run at once
 hipError_t nuts_block_setup(const JobDev& j);
 hipError_t nuts_block_steps(const JobDev& j, int G, int K, uint32_t step, hipStream_t s);
+hipError_t nuts_settle(const JobDev& j, hipStream_t s);  // no leapfrog is left waiting for its gradient
 hipError_t nuts_gradient(const JobDev& j, int mode, uint32_t step, hipStream_t s);  // after nuts_transition(mode, step)
 size_t logreg_split_bytes(const JobDev& j);
 hipError_t logreg_setup(const JobDev& j, hipStream_t s);

@@ -76,6 +76,24 @@ __global__ __launch_bounds__(256) void nuts_step_kernel(NutsK a)
     }
 }
 
+// Finishes the leapfrogs that wait for their gradient, as the next step would, and
+// asks for none: the chains stop before their next leapfrog.
+template <int EPL>
+__global__ __launch_bounds__(256) void nuts_settle_kernel(NutsK a)
+{
+    const int lane = threadIdx.x & 63, c = uni((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (c >= a.m) return;
+    NutsScal S = nuts_load(a, c, uni(a.t[c]));
+    if (S.t >= a.tstop || !(S.fl & NF_PENDING)) return;
+    float* Vc = a.V + (size_t)c * a.nvec * a.Dp;
+    NutsBox<EPL, BOX_MEMORY> box(Vc, a.Dp, lane, Vc + (size_t)V_FIXED * a.Dp);
+    const int64_t budget = S.budget;
+    S.budget = 0;
+    (void)nuts_chain_body<EPL, SliceGrad>(a, SliceGrad{a}, c, lane, S, box);
+    S.budget = budget;
+    nuts_store(a, c, S, 0, lane);
+}
+
 __global__ __launch_bounds__(1024) void nuts_compact_kernel(const int32_t* req, int m, int vmap, int32_t* list,
                                                             int32_t* count, unsigned long long* ctr)
 {
@@ -207,6 +225,17 @@ hipError_t nuts_block_setup(const JobDev& j) { return block_dispatch(j, NutsK{},
 hipError_t nuts_block_steps(const JobDev& j, int G, int K, uint32_t step, hipStream_t s)
 {
     return block_dispatch(j, nuts_view(j, 0, step), G, K, s, false);
+}
+
+hipError_t nuts_settle(const JobDev& j, hipStream_t s)
+{
+    const NutsK a = nuts_view(j, 0, 0);
+    const dim3 grid((j.m + 3) / 4), block(256);
+    if (j.Dp <= 64)
+        hipLaunchKernelGGL(nuts_settle_kernel<1>, grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL(nuts_settle_kernel<2>, grid, block, 0, s, a);
+    return hipGetLastError();
 }
 
 hipError_t nuts_transition(const JobDev& j, int mode, uint32_t step, hipStream_t s)

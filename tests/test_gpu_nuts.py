@@ -310,3 +310,43 @@ def test_launch_per_step_every_dimension_class(F, ctx, D):
         job.free()
     for s, c in ((S1, C1), (S2, C2)):
         assert np.array_equal(S, s) and np.array_equal(C, c)
+
+
+# block kernel; launch per step with the vectors ahead of the step; without (P.th read
+# from the request buffer), several row slices
+@pytest.mark.parametrize("D,N,m", [(10, 1000, 16), (70, 600, 300), (70, 300, 2100)])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_potential_between_a_batch_and_the_next_step(F, ctx, D, N, m, noalloc):
+    """A batch freed in mid-run leaves chains with a leapfrog waiting for its
+    gradient; a call of the potential then must not touch what they wait for:
+    the draws are those of an uninterrupted job, and the call's results those of
+    a fresh job."""
+    d = inputs.logreg(n_data=N, dim=D, seed=8)
+    X = torch.tensor(d["X"], dtype=torch.float32, device="cuda")
+    y = torch.tensor(d["y"], dtype=torch.float32, device="cuda")
+    n, seed, eps, J = 6, 23, 0.1, 5
+    S, C, st = gpu_nuts(F, ctx, d, m, n, seed, eps, J)
+    th = torch.randn(m, D, generator=torch.Generator().manual_seed(9)).cuda()
+    fresh = F.Job(ctx, F.logreg_target(X, y), F.nuts_sampler(eps, J), m, n, seed + 1)
+    try:
+        Ur, gr = fresh.potential(th)
+    finally:
+        fresh.free()
+    job = F.Job(ctx, F.logreg_target(X, y), F.nuts_sampler(eps, J), m, n, seed)
+    try:
+        for piece in (1, 2):  # twice: the first call must also leave a job that a batch can take on
+            b = F.Batch(ctx, [job], nuts_steps=5)
+            assert not b.run(piece)
+            b.free()
+            U, g = torch.empty_like(Ur), torch.empty_like(gr)
+            if noalloc:
+                job.potential_noalloc(th, g, U)
+                job.sync()
+            else:
+                U, g = job.potential(th)
+            assert torch.equal(U, Ur) and torch.equal(g, gr)
+        assert job.step_fsm(0)
+        assert np.array_equal(job.samples(), S) and np.array_equal(job.counts(), C)
+        assert job.stats()["steps"] == st["steps"]
+    finally:
+        job.free()
