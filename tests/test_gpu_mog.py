@@ -207,3 +207,20 @@ def test_mog_waves_per_block(F, ctx, m):
     S, C, _ = run(F, ctx, w, m, 3, 9, 0.05, 4, x0=w["x0"])
     S1, C1, _ = run(F, ctx, w, m, 3, 9, 0.05, 4, x0=w["x0"], runtime="vmap")
     assert np.array_equal(S, S1) and np.array_equal(C, C1)
+
+
+def test_mog_checkpoints_in_memory_equal_those_in_lds(F, ctx):
+    """D = 100 at depth 10: with 5 waves a block (1100 chains) the U-turn
+    checkpoints no longer fit LDS beside the matrix and stay in memory; with 64
+    chains (one wave a block) they are in LDS.  A chain's draws depend on its
+    index and start alone, so the first 64 chains are the same bits either
+    way, whole and in pieces that stop inside draws (the checkpoints then go out
+    and come back)."""
+    m, m0, n, seed = 1100, 64, 4, 77
+    w = inputs.mog(dim=100, n_chains=m, seed=78)
+    S0, C0, _ = run(F, ctx, w, m0, n, seed, 0.0473, 10, x0=w["x0"][:m0])
+    assert C0.max() >= 8  # trees deep enough to use several checkpoints
+    for chains, steps in ((m0, 3), (m, 0), (m, 3)):
+        S, C, st = run(F, ctx, w, chains, n, seed, 0.0473, 10, x0=w["x0"][:chains], max_steps=steps)
+        assert np.array_equal(S[:m0], S0) and np.array_equal(C[:m0], C0)
+        assert np.isfinite(S).all() and st["steps"] == C.sum()
