@@ -183,15 +183,21 @@ static hipError_t device_malloc(fsmmc_ctx* c, void** p, size_t bytes)
     if (e == hipSuccess) return e;
     (void)hipGetLastError();
     idle_release(c);
-    return hipMalloc(p, bytes);
+    e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();  // not for the next launch's check to find
+    return e;
 }
 
-// Device memory of a job.  zero: cleared, else a job's one direction buffer.  Small arrays are cut from zeroed slabs:
-// a job has about twenty, and an allocation, a clear and a free of each were a
-// third of a millisecond.  The budget counts what was asked for.
-static fsmmc_status job_alloc(fsmmc_job* j, size_t bytes, void** p, bool zero = true)
+// Device memory of a job: job_want charges the budget for an array and notes where
+// its pointer goes, job_place allocates what was noted since the last call.  Arrays
+// of up to kSmallArray share one allocation of just their size (each rounded up to
+// 256 bytes) and one clear: a job has about twenty, and an allocation, a clear and a
+// free of each were a third of a millisecond.  zero: cleared, else a job's one
+// direction buffer.
+constexpr size_t kSmallArray = 2u << 20;
+
+static fsmmc_status job_want(fsmmc_job* j, void* where, size_t bytes, bool zero = true)
 {
-    *p = nullptr;
     if (bytes == 0) bytes = 256;
     fsmmc_ctx* c = j->ctx;
     if (c->budget) {
@@ -203,57 +209,52 @@ static fsmmc_status job_alloc(fsmmc_job* j, size_t bytes, void** p, bool zero = 
     } else {
         c->used.fetch_add(bytes);
     }
-    // sixteen arrays of 8 bytes per chain, 256 KiB to 8 MiB
-    const size_t slab = std::min<size_t>(8u << 20, std::max<size_t>(256u << 10, (size_t)j->d.m * 128));
-    const size_t cut = (bytes + 255) & ~(size_t)255;
-    hipError_t e = hipSuccess;
-    if (zero && cut <= slab / 4) {
-        if (j->slab_left < cut) {
-            void* q = nullptr;
-            if (hipMalloc(&q, slab) == hipSuccess) {
-                j->allocs.push_back(q);
-                j->slab = (unsigned char*)q;
-                j->slab_left = slab;
-                e = hipMemsetAsync(q, 0, slab, j->stream);
-            } else {
-                (void)hipGetLastError();  // the array alone may still fit
-            }
-        }
-        if (j->slab_left >= cut) {
-            *p = j->slab;
-            j->slab += cut;
-            j->slab_left -= cut;
-        }
-    }
-    if (!*p && !zero) {
-        size_t got = bytes;
-        *p = c->budget ? nullptr : idle_take(c, bytes, &got);
-        if (!*p) e = device_malloc(c, p, bytes);
-        if (e != hipSuccess) {
-            c->used.fetch_sub(bytes);
-            *p = nullptr;
-            return fail(FSMMC_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
-        }
-        j->dirs = *p;
-        j->dirs_bytes = got;
-    } else if (!*p) {
-        e = device_malloc(c, p, bytes);
-        if (e != hipSuccess) {
-            c->used.fetch_sub(bytes);
-            *p = nullptr;
-            return fail(FSMMC_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
-        }
-        j->allocs.push_back(*p);
-        e = hipMemsetAsync(*p, 0, bytes, j->stream);
-    }
     j->bytes += bytes;
-    if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
+    j->wants.push_back({where, bytes, zero});
     return FSMMC_OK;
 }
 
-static fsmmc_status job_alloc_to(fsmmc_job* j, void** p, size_t bytes, bool zero = true)
+static fsmmc_status job_place(fsmmc_job* j)
 {
-    return job_alloc(j, bytes, p, zero);
+    const auto cut = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const auto take = [&](size_t bytes, void** p) {
+        hipError_t e = device_malloc(j->ctx, p, bytes);
+        if (e == hipSuccess) j->allocs.push_back(*p);
+        return e;
+    };
+    const auto no_memory = [](hipError_t e) {
+        return fail(FSMMC_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
+    };
+    size_t small = 0;
+    for (const fsmmc_job::Want& w : j->wants) small += w.zero && w.bytes <= kSmallArray ? cut(w.bytes) : 0;
+    unsigned char* next = nullptr;
+    if (small) {
+        void* p = nullptr;
+        hipError_t e = take(small, &p);
+        if (e != hipSuccess) return no_memory(e);
+        HIP_TRY(hipMemsetAsync(p, 0, small, j->stream));
+        next = (unsigned char*)p;
+    }
+    for (const fsmmc_job::Want& w : j->wants) {
+        void* p = nullptr;
+        if (!w.zero) {
+            j->dirs_bytes = w.bytes;
+            p = j->ctx->budget ? nullptr : idle_take(j->ctx, w.bytes, &j->dirs_bytes);
+            hipError_t e = p ? hipSuccess : device_malloc(j->ctx, &p, w.bytes);
+            if (e != hipSuccess) return no_memory(e);
+            j->dirs = p;
+        } else if (w.bytes <= kSmallArray) {
+            p = next;
+            next += cut(w.bytes);
+        } else {
+            hipError_t e = take(w.bytes, &p);
+            if (e != hipSuccess) return no_memory(e);
+            HIP_TRY(hipMemsetAsync(p, 0, w.bytes, j->stream));
+        }
+        std::memcpy(w.where, &p, sizeof(p));
+    }
+    j->wants.clear();
+    return FSMMC_OK;
 }
 
 // The job's pinned words: a slot of the context's page, or an allocation.
@@ -330,16 +331,18 @@ static void job_release(fsmmc_job* j)
     delete j;
 }
 
-#define ALLOC(ptr, ...)                                                 \
-    do {                                                                \
-        void* p__ = nullptr;                                            \
-        fsmmc_status s__ = job_alloc_to(job, &p__, __VA_ARGS__);        \
-        if (s__ != FSMMC_OK) {                                          \
-            job_release(job);                                           \
-            return s__;                                                 \
-        }                                                               \
-        ptr = reinterpret_cast<decltype(ptr)>(p__);                     \
+#define TRY_JOB(expr)                    \
+    do {                                 \
+        fsmmc_status s__ = (expr);       \
+        if (s__ != FSMMC_OK) {           \
+            job_release(job);            \
+            return s__;                  \
+        }                                \
     } while (0)
+
+// Device memory for pointer `ptr`, set by the next PLACE()
+#define ALLOC(ptr, ...) TRY_JOB(job_want(job, &(ptr), __VA_ARGS__))
+#define PLACE() TRY_JOB(job_place(job))
 
 #define HIP_TRY_JOB(expr)                                               \
     do {                                                                \
@@ -539,11 +542,13 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         ALLOC(d.queue, 64);
         ALLOC(d.X, (size_t)d.N * d.pdim * 8);
         ALLOC(d.y, (size_t)d.N * 8);
+        ALLOC(d.L, gph_dist_bytes(d.N));
+        HIP_TRY_JOB(gph_setup(d));
+        if (gph_slot_bytes(d)) ALLOC(d.gslot, gph_slot_bytes(d));
+        PLACE();
         HIP_TRY_JOB(hipMemcpyAsync(d.X, target->X, (size_t)d.N * d.pdim * 8, hipMemcpyDeviceToDevice, job->stream));
         HIP_TRY_JOB(hipMemcpyAsync(d.y, target->y, (size_t)d.N * 8, hipMemcpyDeviceToDevice, job->stream));
-        ALLOC(d.L, gph_dist_bytes(d.N));
-        HIP_TRY_JOB(gph_setup(d, job->stream));
-        if (gph_slot_bytes(d)) ALLOC(d.gslot, gph_slot_bytes(d));
+        HIP_TRY_JOB(gph_dist(d, job->stream));
         HIP_TRY_JOB(gph_init_state(d, x0, job->stream));
         job->launches += x0 ? 2 : 1;
     } else if (d.kind == FSMMC_ESS) {
@@ -572,6 +577,7 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         d.Wcap = d.W;
         ALLOC(d.nu, 2 * m * (size_t)d.W * Dp * es, false);  // a window is filled before it is read
         ALLOC(d.tsnap, m * 4);
+        PLACE();
         // chol_L is read as a synchronous copy would read it: after the work of the
         // null stream, and done when this returns
         HIP_TRY_JOB(hipStreamSynchronize(nullptr));
@@ -613,6 +619,7 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         ALLOC(d.maxN, 2 * (size_t)d.n * 4);
         ALLOC(d.sink, m * 4);
         ALLOC(d.prec, (size_t)d.D * 4);
+        PLACE();
         if (target->kind == FSMMC_GAUSS_DIAG)
             HIP_TRY_JOB(hipMemcpyAsync(d.prec, target->prec, (size_t)d.D * 4, hipMemcpyDeviceToDevice, job->stream));
         hipLaunchKernelGGL(fill_i32_kernel, dim3((d.m + 255) / 256), dim3(256), 0, job->stream, d.k, 1, d.m);
@@ -634,6 +641,7 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         ALLOC(d.maxN, (size_t)d.n * 4);
         ALLOC(d.sink, m * 4);
         ALLOC(d.prec, (size_t)d.D * 4);
+        PLACE();
         if (target->kind == FSMMC_GAUSS_DIAG)
             HIP_TRY_JOB(hipMemcpyAsync(d.prec, target->prec, (size_t)d.D * 4, hipMemcpyDeviceToDevice, job->stream));
         HIP_TRY_JOB(drs_init_state(d, x0, job->stream));
@@ -647,6 +655,7 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         ALLOC(d.maxN, (size_t)d.n * 4);
         ALLOC(d.sink, m * 4);
         ALLOC(d.prec, (size_t)d.D * 4);
+        PLACE();
         if (target->kind == FSMMC_GAUSS_DIAG)
             HIP_TRY_JOB(hipMemcpyAsync(d.prec, target->prec, (size_t)d.D * 4, hipMemcpyDeviceToDevice, job->stream));
         hipLaunchKernelGGL(fill_i32_kernel, dim3((d.m + 255) / 256), dim3(256), 0, job->stream, d.k, 1, d.m);
@@ -680,6 +689,7 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         ALLOC(d.y, (size_t)d.K * 4);
         ALLOC(d.mogB, (size_t)d.K * Dp * 8);
         ALLOC(d.mogC, (size_t)d.K * 8);
+        PLACE();
         HIP_TRY_JOB(hipMemcpy2DAsync(d.prec, Dp * 4, target->prec, (size_t)d.D * 4, (size_t)d.D * 4, (size_t)d.D,
                                      hipMemcpyDeviceToDevice, job->stream));
         HIP_TRY_JOB(hipMemcpyAsync(d.X, target->X, (size_t)d.K * d.D * 4, hipMemcpyDeviceToDevice, job->stream));
@@ -736,6 +746,7 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         ALLOC(d.X, (size_t)d.Np * Dp * 4);
         ALLOC(d.Xb, logreg_split_bytes(d));
         ALLOC(d.y, (size_t)d.Np * 4);
+        PLACE();
         HIP_TRY_JOB(hipMemcpy2DAsync(d.X, Dp * 4, target->X, (size_t)d.D * 4, (size_t)d.D * 4, (size_t)d.N,
                                      hipMemcpyDeviceToDevice, job->stream));
         HIP_TRY_JOB(hipMemcpyAsync(d.y, target->y, (size_t)d.N * 4, hipMemcpyDeviceToDevice, job->stream));

@@ -73,8 +73,12 @@ struct fsmmc_job {
     size_t bytes = 0;
     void* dirs = nullptr;  // the direction buffer (kept by the context when the job is freed)
     size_t dirs_bytes = 0;
-    unsigned char* slab = nullptr;  // zeroed memory not handed out yet (job_alloc)
-    size_t slab_left = 0;
+    struct Want {
+        void* where;  // the pointer to set
+        size_t bytes;
+        bool zero;
+    };
+    std::vector<Want> wants;  // charged, not allocated yet (job_place)
     unsigned long long* h_ctr = nullptr;  // pinned: [0..7] mirror of d.ctr, [8..15] scratch reads
     int launches = 0;
     uint32_t step = 0;  // NUTS runtime step counter (keys the per-step counters)

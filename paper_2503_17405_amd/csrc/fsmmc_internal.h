@@ -145,7 +145,8 @@ int gph_max_obs();
 size_t gph_slot_bytes(const JobDev& j);  // after gph_setup
 size_t gph_dist_bytes(int N);            // squared distances of the inputs (j.L)
 int gph_max_inputs();
-hipError_t gph_setup(JobDev& j, hipStream_t s);
+hipError_t gph_setup(JobDev& j);
+hipError_t gph_dist(const JobDev& j, hipStream_t s);
 hipError_t gph_init_state(const JobDev& j, const void* x0, hipStream_t s);
 hipError_t gph_run(const JobDev& j, int mode, uint32_t draw, unsigned long long* ticket, hipStream_t s);
 

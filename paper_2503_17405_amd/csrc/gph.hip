@@ -782,12 +782,16 @@ size_t gph_dist_bytes(int N)
     return R * (R + 1) / 2 * kGphTile * 8;
 }
 
-// Launch shape, and the squared distances (into j.L, after X is in place).
-hipError_t gph_setup(JobDev& j, hipStream_t s)
+// Launch shape.
+hipError_t gph_setup(JobDev& j)
 {
     j.pwpb = gph_waves(j.N);
-    hipError_t e = gph_blocks(j, &j.pblocks);
-    if (e != hipSuccess) return e;
+    return gph_blocks(j, &j.pblocks);
+}
+
+// The squared distances (into j.L, after X is in place).
+hipError_t gph_dist(const JobDev& j, hipStream_t s)
+{
     const int R = (j.N + 16) / 16;
     hipLaunchKernelGGL(gph_dist_kernel, dim3(R * (R + 1) / 2), dim3(256), 0, s, (const double*)j.X, j.N, j.pdim,
                        (double*)j.L);

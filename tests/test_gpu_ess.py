@@ -305,3 +305,27 @@ def test_ess_many_jobs_share_a_context(F):
         assert c.bytes_in_use() == 0
     finally:
         c.close()
+
+
+def test_small_jobs_hold_what_the_budget_counts(F):
+    """The budget bounds the device memory of a context's jobs: what many small
+    jobs take from the device is what is counted for them, up to the rounding of
+    about twenty arrays to 256 bytes, one 4 KiB page a job and the driver's 2 MiB
+    blocks."""
+    t, s, jobs = F.funnel_target(2), F.dr_sampler(), 400
+    out = torch.zeros((1, 1, 2), device="cuda")
+    ctx = F.Context(0, hbm_budget_bytes=1 << 20)
+    held = []
+    try:
+        held.append(F.Job(ctx, t, s, 1, 1, 1, out=out))
+        torch.cuda.synchronize()
+        before, counted = torch.cuda.mem_get_info()[0], ctx.bytes_in_use()
+        held += [F.Job(ctx, t, s, 1, 1, 1, out=out) for _ in range(jobs)]
+        torch.cuda.synchronize()
+        taken, counted = before - torch.cuda.mem_get_info()[0], ctx.bytes_in_use() - counted
+        assert 0 < counted < 1 << 20
+        assert taken <= counted + jobs * (20 * 256 + 4096) + (4 << 20)
+    finally:
+        for j in held:
+            j.free()
+        ctx.close()
