@@ -542,13 +542,13 @@ fsmmc_status fsmmc_init_chains(fsmmc_ctx* ctx, const fsmmc_target_spec* target,
         ALLOC(d.queue, 64);
         ALLOC(d.X, (size_t)d.N * d.pdim * 8);
         ALLOC(d.y, (size_t)d.N * 8);
-        ALLOC(d.L, gph_dist_bytes(d.N));
         HIP_TRY_JOB(gph_setup(d));
+        if (gph_keeps_dist(d, ctx->budget != 0)) ALLOC(d.L, gph_dist_bytes(d.N));
         if (gph_slot_bytes(d)) ALLOC(d.gslot, gph_slot_bytes(d));
         PLACE();
         HIP_TRY_JOB(hipMemcpyAsync(d.X, target->X, (size_t)d.N * d.pdim * 8, hipMemcpyDeviceToDevice, job->stream));
         HIP_TRY_JOB(hipMemcpyAsync(d.y, target->y, (size_t)d.N * 8, hipMemcpyDeviceToDevice, job->stream));
-        HIP_TRY_JOB(gph_dist(d, job->stream));
+        if (d.L) HIP_TRY_JOB(gph_dist(d, job->stream));
         HIP_TRY_JOB(gph_init_state(d, x0, job->stream));
         job->launches += x0 ? 2 : 1;
     } else if (d.kind == FSMMC_ESS) {

@@ -144,6 +144,7 @@ hipError_t mog_eval(const JobDev& j, int n, const float* pts, float* G, float* U
 int gph_max_obs();
 size_t gph_slot_bytes(const JobDev& j);  // after gph_setup
 size_t gph_dist_bytes(int N);            // squared distances of the inputs (j.L)
+bool gph_keeps_dist(const JobDev& j, bool budget);  // after gph_setup
 int gph_max_inputs();
 hipError_t gph_setup(JobDev& j);
 hipError_t gph_dist(const JobDev& j, hipStream_t s);

@@ -13,7 +13,8 @@
 // of smooth kernels are badly conditioned; the 3-D chain state is FP64 too) on
 // the matrix cores, from 16 x 16 tiles held in registers (gph_loglik below).
 // The squared distances |x_i - x_k|^2 do not depend on theta: they are formed
-// once per job (gph_dist_kernel), laid out tile by tile as the lanes read them.
+// once per job (gph_dist_kernel), laid out tile by tile as the lanes read them
+// (but for small jobs under an HBM budget, gph_keeps_dist).
 // The library builds with contraction off, so the updates are written as
 // explicit FMAs (one instruction and one rounding per term).
 // The synchronized runtime launches the kernel once per draw (tstop =
@@ -36,7 +37,8 @@ struct GphK {
     uint64_t seed;
     double jitter;
     const double* y;   // N outputs
-    const double* r2;  // squared distances, tile (I, J <= I) at I (I + 1) / 2 + J (gph_dist_kernel)
+    const double* X;   // N x p inputs
+    const double* r2;  // squared distances, tile (I, J <= I) at I (I + 1) / 2 + J (gph_dist_kernel), or NULL
     double *th, *nu;  // [chain][3]
     double *lx, *phi, *pmin, *pmax, *logu;
     int32_t *k, *evals;
@@ -228,12 +230,29 @@ __device__ __forceinline__ void gph_factor(const d4& acc, int nc, int yrow, int 
     __builtin_amdgcn_s_setprio(0);
 }
 
+// The squared distance of inputs i and k (0 past the last).
+__device__ __forceinline__ double gph_dist2(const double* X, int N, int p, int i, int k)
+{
+    double s = 0.0;
+    if (i < N && k < N)
+        for (int d = 0; d < p; ++d) {
+            const double e = X[i * p + d] - X[k * p + d];
+            s = fma(e, e, s);
+        }
+    return s;
+}
+
 // Minus tile (I, J) of C (with y as row n).
 __device__ __forceinline__ d4 gph_tile_of_c(const GphK& a, double tau2, double lam2, double s2, int I, int J, int lane)
 {
     const int row = 16 * I + (lane & 15), col0 = 16 * J + (lane >> 4);
-    const d4 r2 = tile_load(a.r2 + (size_t)(I * (I + 1) / 2 + J) * kGphTile, lane);
-    d4 v;
+    d4 v, r2;
+    if (a.r2) {
+        r2 = tile_load(a.r2 + (size_t)(I * (I + 1) / 2 + J) * kGphTile, lane);
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) r2[r] = gph_dist2(a.X, a.N, a.p, row, col0 + 4 * r);
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[r] = -(tau2 * exp(-lam2 * r2[r]) + (row == col0 + 4 * r ? s2 : 0.0));
     if (16 * I + 16 > a.N) {  // the tile row that holds row n and the padding below it
@@ -468,14 +487,8 @@ __global__ __launch_bounds__(256) void gph_dist_kernel(const double* X, int N, i
     while (I * (I + 1) / 2 > (int)blockIdx.x) --I;
     const int J = (int)blockIdx.x - I * (I + 1) / 2;
     const int lane = threadIdx.x & 63, r = threadIdx.x >> 6;
-    const int i = 16 * I + (lane & 15), k = 16 * J + (lane >> 4) + 4 * r;
-    double s = 0.0;
-    if (i < N && k < N)
-        for (int d = 0; d < p; ++d) {
-            const double e = X[i * p + d] - X[k * p + d];
-            s = fma(e, e, s);
-        }
-    r2[(size_t)blockIdx.x * kGphTile + ((r >> 1) * 64 + lane) * 2 + (r & 1)] = s;
+    r2[(size_t)blockIdx.x * kGphTile + ((r >> 1) * 64 + lane) * 2 + (r & 1)] =
+        gph_dist2(X, N, p, 16 * I + (lane & 15), 16 * J + (lane >> 4) + 4 * r);
 }
 
 // A chain's state while the block steps it, in LDS: the likelihood needs every
@@ -711,6 +724,7 @@ static GphK gph_view(const JobDev& j)
     a.seed = j.seed;
     a.jitter = j.noise_sd;
     a.y = (const double*)j.y;
+    a.X = (const double*)j.X;
     a.r2 = (const double*)j.L;
     a.th = (double*)j.x;
     a.nu = (double*)j.V;
@@ -780,6 +794,19 @@ size_t gph_dist_bytes(int N)
 {
     const size_t R = (size_t)(N + 16) / 16;
     return R * (R + 1) / 2 * kGphTile * 8;
+}
+
+// Whether a job keeps the squared distances.  Under an HBM budget only where it then
+// holds no more than the vector Cholesky before this one did (a work matrix of n
+// rounded up to 32 per block above n = 96, nothing up to there), so that what
+// fitted a budget still does; the kernels form the distances themselves otherwise
+// (6 inputs: n = 25, 1024 chains x 100 draws 4.0 -> 6.1 ms, n = 63, 512 x 60 8.5 ->
+// 12.2, n = 96, 1024 x 40 13.9 -> 18.7).
+bool gph_keeps_dist(const JobDev& j, bool budget)
+{
+    const size_t ld = (size_t)(j.N + 31) / 32 * 32;
+    const size_t before = j.N > 96 ? (size_t)std::min(j.m, 256) * ld * ld * 8 : 0;
+    return !budget || gph_slot_bytes(j) + gph_dist_bytes(j.N) <= before;
 }
 
 // Launch shape.

@@ -137,3 +137,22 @@ def test_gphyper_singular_start(F, ctx, nobs):
     R, RC, _ = O.run_chains(tg, sp, seed, range(m), n, x0=x0)
     assert np.array_equal(C, RC) and np.all(C[:, 0] == 1)
     assert np.abs(S - R).max() <= 1e-9
+
+
+@pytest.mark.parametrize("nobs,m", [(5, 3), (31, 2), (64, 16), (96, 7), (97, 1), (100, 30), (128, 2), (300, 1), (512, 1), (512, 9)])
+def test_gphyper_under_a_budget(F, ctx, nobs, m):
+    """A budget of the chain state, the data and (above 96 observations) a work
+    matrix per chain is enough at every size: where the squared distances do not
+    fit it, the kernels form them, with the same bits."""
+    n, seed = 4, 91
+    w = inputs.gp_hyper(n=nobs, n_chains=m, seed=92)
+    S0, C0, _ = run(F, ctx, w, m, n, seed, x0=w["x0"])
+    N, p, ld = nobs, w["X"].shape[1], (nobs + 31) // 32 * 32
+    state = m * (3 * 4 + 8 + 8 + 4 * n + n * 24 + 2 * 24 + 5 * 8) + 64 + 4 * n + 64 + N * p * 8 + N * 8
+    tight = F.Context(0, hbm_budget_bytes=state + (m * ld * ld * 8 if N > 96 else 0))
+    try:
+        for runtime, steps in (("fsm", 0), ("vmap", 0)):
+            S, C, _ = run(F, tight, w, m, n, seed, runtime, steps, x0=w["x0"])
+            assert np.array_equal(S, S0) and np.array_equal(C, C0)
+    finally:
+        tight.close()
