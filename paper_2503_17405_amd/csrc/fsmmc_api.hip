@@ -116,14 +116,13 @@ __global__ void unpack_potential_kernel(const float* g, const float* u, float* o
 }
 }  // namespace
 
-// Whether kernels can read and write memory at p (device, managed or pinned).
-static bool kernel_reaches(const void* p)
+// Whether kernels on `device` can read and write memory at p.
+static bool kernel_reaches(const void* p, int device)
 {
     hipPointerAttribute_t a{};
-    const bool ok = hipPointerGetAttributes(&a, p) == hipSuccess && a.devicePointer == p &&
-                    (a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeHost || a.type == hipMemoryTypeManaged);
-    if (!ok) (void)hipGetLastError();
-    return ok;
+    if (hipPointerGetAttributes(&a, p) == hipSuccess) return reaches(a, p, device);
+    (void)hipGetLastError();
+    return false;
 }
 
 // Device address of `scratch` on `device` (the current device), looked up
@@ -1264,7 +1263,8 @@ fsmmc_status fsmmc_eval_potential(fsmmc_job* job, int32_t n_points, const void* 
     // copied.
     const size_t bt = (size_t)n_points * d.D * 4, bu = (size_t)n_points * 4, np = (size_t)n_points * d.Dp;
     unsigned char* tmp = nullptr;
-    if (!kernel_reaches(theta) || !kernel_reaches(U) || (grad && !kernel_reaches(grad))) {
+    const int dev = job->ctx->device;
+    if (!kernel_reaches(theta, dev) || !kernel_reaches(U, dev) || (grad && !kernel_reaches(grad, dev))) {
         HIP_TRY(hipMalloc((void**)&tmp, 2 * bt + bu));
     }
     const float* th = tmp ? (const float*)tmp : (const float*)theta;

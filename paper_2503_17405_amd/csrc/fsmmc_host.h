@@ -52,6 +52,16 @@ fsmmc_status hip_fail(hipError_t e, const char* what);
 // Argument checks of fsmmc_init_chains (sets the error message).
 fsmmc_status validate_specs(const fsmmc_target_spec* t, const fsmmc_sampler_spec* s, int32_t m, int32_t n);
 
+// Whether memory at p with attributes a may be passed to kernels on `device`: its own
+// device memory (another device's needs peer access, which nobody has asked for),
+// managed, or pinned at the same address.
+inline bool reaches(const hipPointerAttribute_t& a, const void* p, int device)
+{
+    if (a.devicePointer != p) return false;
+    if (a.type == hipMemoryTypeDevice) return a.device == device;
+    return a.type == hipMemoryTypeHost || a.type == hipMemoryTypeManaged;
+}
+
 hipError_t fill_i64(int64_t* p, int64_t v, int n, hipStream_t s);
 hipError_t fill_i32(int32_t* p, int32_t v, int n, hipStream_t s);
 
