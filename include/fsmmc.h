@@ -192,6 +192,14 @@ fsmmc_status fsmmc_ctx_destroy(fsmmc_ctx* ctx);
 /* Bytes of device memory the context's jobs hold now. */
 size_t fsmmc_ctx_bytes_in_use(const fsmmc_ctx* ctx);
 
+/* ESS direction buffers of freed jobs stay allocated for the next jobs, up to
+ * 1 GiB a device (the oldest are freed for newer ones) and only those of contexts
+ * without a budget; fsmmc_ctx_bytes_in_use does not count them.  They go back to
+ * the device when its last context is destroyed, when an allocation of this
+ * library on the device fails (it is then tried again), and at this call, for
+ * callers that need the memory elsewhere.  Errors: EINVAL. */
+fsmmc_status fsmmc_ctx_trim(fsmmc_ctx* ctx);
+
 /* Create a job of n_chains chains that will each produce n_draws draws, and
  * initialise every chain (Alg. "FSM MCMC algorithm", initialisation: z =
  * init(x0), t = 0, k = S_1).
@@ -304,7 +312,8 @@ fsmmc_status fsmmc_job_stats(fsmmc_job* job, fsmmc_stats* out);
 /* Block until the job's queued work has finished. */
 fsmmc_status fsmmc_job_sync(fsmmc_job* job);
 
-/* Release a job and its device memory (waits for its queued work first). */
+/* Release a job and its device memory (waits for its queued work first); an
+ * ESS job's direction buffer may be kept for later jobs (fsmmc_ctx_trim). */
 fsmmc_status fsmmc_job_free(fsmmc_job* job);
 
 /* ---------------------------------------------------------------- batching

@@ -326,7 +326,7 @@ fsmmc_status ensure(T** p, size_t* cap, size_t n)
     if (*p) (void)hipFree(*p);
     *p = nullptr;
     *cap = 0;
-    HIP_TRY(hipMalloc((void**)p, want * sizeof(T)));
+    HIP_TRY(device_malloc((void**)p, want * sizeof(T)));
     *cap = want;
     return FSMMC_OK;
 }
@@ -341,7 +341,7 @@ fsmmc_status ensure_stat(fsmmc_batch* b, size_t njobs)
     b->h_stat = nullptr;
     b->cap_stat = 0;
     const size_t want = stat_bytes(std::max<size_t>(njobs, 16) * 2);
-    HIP_TRY(hipMalloc((void**)&b->d_stat, want));
+    HIP_TRY(device_malloc((void**)&b->d_stat, want));
     HIP_TRY(hipHostMalloc((void**)&b->h_stat, want, hipHostMallocDefault));
     b->cap_stat = want;
     return FSMMC_OK;

@@ -141,9 +141,9 @@ extern "C" fsmmc_status fsmmc_measure_ceilings(int device, size_t copy_bytes, fs
     const int blocks = p.multiProcessorCount * 8, threads = 256;  // 8 waves per SIMD
     const double waves = (double)blocks * threads / 64.0;
     void *src = nullptr, *dst = nullptr, *res = nullptr;
-    hipError_t e = hipMalloc(&src, copy_bytes);
-    if (e == hipSuccess) e = hipMalloc(&dst, copy_bytes);
-    if (e == hipSuccess) e = hipMalloc(&res, (size_t)blocks * threads * sizeof(double));
+    hipError_t e = device_malloc(&src, copy_bytes);
+    if (e == hipSuccess) e = device_malloc(&dst, copy_bytes);
+    if (e == hipSuccess) e = device_malloc(&res, (size_t)blocks * threads * sizeof(double));
     if (e == hipSuccess) e = hipMemset(src, 0, copy_bytes);
     double ms = 0.0;
     if (e == hipSuccess) {

@@ -141,49 +141,39 @@ static fsmmc_status scratch_setup(int device, void** out)
     return FSMMC_OK;
 }
 
-// Idle buffers back to the device (an allocation that fails is tried again after).
-static void idle_release(fsmmc_ctx* c)
+// The idle buffers of a device's freed jobs.
+static IdlePool* idle_pool(int device)
 {
-    std::lock_guard<std::mutex> lk(c->mu);
-    for (const fsmmc_ctx::Idle& b : c->idle) (void)hipFree(b.p);
-    c->idle.clear();
-    c->idle_bytes = 0;
+    static constexpr size_t kIdleBytes = (size_t)1 << 30;
+    static std::mutex mu;
+    static IdlePool* pools[kMaxDevices] = {};  // until the process ends
+    if (device < 0 || device >= kMaxDevices) return nullptr;
+    std::lock_guard<std::mutex> lk(mu);
+    if (!pools[device]) pools[device] = new IdlePool(kIdleBytes, [](void* p) { (void)hipFree(p); });
+    return pools[device];
 }
 
-// An idle buffer of at least `bytes` and at most a quarter more, or NULL.
-static void* idle_take(fsmmc_ctx* c, size_t bytes, size_t* got)
-{
-    std::lock_guard<std::mutex> lk(c->mu);
-    for (size_t i = 0; i < c->idle.size(); ++i) {
-        const fsmmc_ctx::Idle b = c->idle[i];
-        if (b.bytes < bytes || b.bytes > bytes + bytes / 4) continue;
-        c->idle.erase(c->idle.begin() + i);
-        c->idle_bytes -= b.bytes;
-        *got = b.bytes;
-        return b.p;
-    }
-    return nullptr;
-}
-
-// Keeps an unused buffer if there is room (nothing on the device may use it any more).
-static bool idle_give(fsmmc_ctx* c, void* p, size_t bytes)
-{
-    if (c->budget) return false;
-    std::lock_guard<std::mutex> lk(c->mu);
-    if (c->idle_bytes + bytes > fsmmc_ctx::kIdleBytes) return false;
-    c->idle.push_back({p, bytes});
-    c->idle_bytes += bytes;
-    return true;
-}
-
-static hipError_t device_malloc(fsmmc_ctx* c, void** p, size_t bytes)
+hipError_t fsmmc::device_malloc(void** p, size_t bytes)
 {
     hipError_t e = hipMalloc(p, bytes);
     if (e == hipSuccess) return e;
     (void)hipGetLastError();
-    idle_release(c);
+    int device = -1;
+    if (hipGetDevice(&device) == hipSuccess)
+        if (IdlePool* q = idle_pool(device)) q->release();
     e = hipMalloc(p, bytes);
     if (e != hipSuccess) (void)hipGetLastError();  // not for the next launch's check to find
+    return e;
+}
+
+// Waits for all work on `device`; the current device stays.
+static hipError_t device_sync(int device)
+{
+    int old = device;
+    (void)hipGetDevice(&old);
+    hipError_t e = old == device ? hipSuccess : hipSetDevice(device);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (old != device) (void)hipSetDevice(old);
     return e;
 }
 
@@ -217,7 +207,7 @@ static fsmmc_status job_place(fsmmc_job* j)
 {
     const auto cut = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const auto take = [&](size_t bytes, void** p) {
-        hipError_t e = device_malloc(j->ctx, p, bytes);
+        hipError_t e = device_malloc(p, bytes);
         if (e == hipSuccess) j->allocs.push_back(*p);
         return e;
     };
@@ -238,8 +228,8 @@ static fsmmc_status job_place(fsmmc_job* j)
         void* p = nullptr;
         if (!w.zero) {
             j->dirs_bytes = w.bytes;
-            p = j->ctx->budget ? nullptr : idle_take(j->ctx, w.bytes, &j->dirs_bytes);
-            hipError_t e = p ? hipSuccess : device_malloc(j->ctx, &p, w.bytes);
+            p = j->ctx->budget ? nullptr : j->ctx->idle->take(w.bytes, &j->dirs_bytes);
+            hipError_t e = p ? hipSuccess : device_malloc(&p, w.bytes);
             if (e != hipSuccess) return no_memory(e);
             j->dirs = p;
         } else if (w.bytes <= kSmallArray) {
@@ -312,7 +302,8 @@ static void job_release(fsmmc_job* j)
         (void)hipStreamSynchronize(j->side);
         (void)hipStreamDestroy(j->side);
     }
-    if (j->dirs && !(hipDeviceSynchronize() == hipSuccess && idle_give(j->ctx, j->dirs, j->dirs_bytes)))
+    if (j->dirs && !(!j->ctx->budget && device_sync(j->ctx->device) == hipSuccess &&
+                     j->ctx->idle->give(j->dirs, j->dirs_bytes)))
         (void)hipFree(j->dirs);
     for (void* p : j->allocs) (void)hipFree(p);
     pinned_give(j);
@@ -372,6 +363,8 @@ fsmmc_status fsmmc_ctx_create(int device, size_t hbm_budget_bytes, fsmmc_ctx** o
     fsmmc_ctx* c = new fsmmc_ctx();
     c->device = device;
     c->budget = hbm_budget_bytes;
+    c->idle = idle_pool(device);
+    c->idle->open();
     *out = c;
     return FSMMC_OK;
 }
@@ -380,9 +373,16 @@ fsmmc_status fsmmc_ctx_destroy(fsmmc_ctx* ctx)
 {
     if (!ctx) return fail(FSMMC_EINVAL, "ctx is NULL");
     if (ctx->jobs.load() != 0) return fail(FSMMC_EBUSY, "context still has jobs");
-    idle_release(ctx);
+    ctx->idle->close();
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     delete ctx;
+    return FSMMC_OK;
+}
+
+fsmmc_status fsmmc_ctx_trim(fsmmc_ctx* ctx)
+{
+    if (!ctx) return fail(FSMMC_EINVAL, "ctx is NULL");
+    ctx->idle->release();
     return FSMMC_OK;
 }
 
@@ -1265,7 +1265,7 @@ fsmmc_status fsmmc_eval_potential(fsmmc_job* job, int32_t n_points, const void* 
     unsigned char* tmp = nullptr;
     const int dev = job->ctx->device;
     if (!kernel_reaches(theta, dev) || !kernel_reaches(U, dev) || (grad && !kernel_reaches(grad, dev))) {
-        HIP_TRY(hipMalloc((void**)&tmp, 2 * bt + bu));
+        HIP_TRY(device_malloc((void**)&tmp, 2 * bt + bu));
     }
     const float* th = tmp ? (const float*)tmp : (const float*)theta;
     float* g = tmp && grad ? (float*)(tmp + bt) : (float*)grad;

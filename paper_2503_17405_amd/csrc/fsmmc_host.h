@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "fsmmc_internal.h"
+#include "idle_pool.h"
 
 struct fsmmc_batch;
 
@@ -22,16 +23,10 @@ struct fsmmc_ctx {
     // allocation of each costs more than a small job's kernels).  Released with
     // the context, which outlives its jobs.
     static constexpr int kPinnedSlots = 32;  // of 16 64-bit words
-    // Direction buffers of freed jobs, at most kIdleBytes, for the next jobs of a
-    // context without a budget: freeing and allocating hundreds of MiB every few
-    // milliseconds stalls in the driver (a batch of 8 ms took 19 to 60).
-    static constexpr size_t kIdleBytes = (size_t)1 << 30;
-    struct Idle {
-        void* p;
-        size_t bytes;
-    };
-    std::vector<Idle> idle;
-    size_t idle_bytes = 0;
+    // Direction buffers of freed jobs of contexts without a budget: freeing and
+    // allocating hundreds of MiB every few milliseconds stalls in the driver (a batch
+    // of 8 ms took 19 to 60).
+    fsmmc::IdlePool* idle = nullptr;
     std::mutex mu;
     unsigned long long* pinned = nullptr;
     uint32_t pinned_free = 0;  // bit i: slot i is free
@@ -61,6 +56,9 @@ inline bool reaches(const hipPointerAttribute_t& a, const void* p, int device)
     if (a.type == hipMemoryTypeDevice) return a.device == device;
     return a.type == hipMemoryTypeHost || a.type == hipMemoryTypeManaged;
 }
+
+// hipMalloc on the current device; if that fails, once more without its idle buffers.
+hipError_t device_malloc(void** p, size_t bytes);
 
 hipError_t fill_i64(int64_t* p, int64_t v, int n, hipStream_t s);
 hipError_t fill_i32(int32_t* p, int32_t v, int n, hipStream_t s);

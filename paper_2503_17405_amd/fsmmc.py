@@ -24,7 +24,7 @@ SYNC_VMAP, SYNC_COMPACT = 0, 1
 
 # every symbol the header declares
 EXPORTS = [
-    "fsmmc_ctx_create", "fsmmc_ctx_destroy", "fsmmc_ctx_bytes_in_use", "fsmmc_init_chains",
+    "fsmmc_ctx_create", "fsmmc_ctx_destroy", "fsmmc_ctx_bytes_in_use", "fsmmc_ctx_trim", "fsmmc_init_chains",
     "fsmmc_step_fsm", "fsmmc_step_fsm_async", "fsmmc_step_synchronized", "fsmmc_collect_samples",
     "fsmmc_collect_counts",
     "fsmmc_chain_progress", "fsmmc_job_stats", "fsmmc_job_sync", "fsmmc_job_free",
@@ -128,6 +128,7 @@ def _load():
         "fsmmc_ctx_create": ([C.c_int, sz, pp], C.c_int),
         "fsmmc_ctx_destroy": ([p], C.c_int),
         "fsmmc_ctx_bytes_in_use": ([p], sz),
+        "fsmmc_ctx_trim": ([p], C.c_int),
         "fsmmc_init_chains": ([p, p, p, i32, i32, u64, p, p, p, p, pp], C.c_int),
         "fsmmc_step_fsm": ([p, i64, p], C.c_int),
         "fsmmc_step_fsm_async": ([p, i64, p], C.c_int),
@@ -308,6 +309,10 @@ class Context:
 
     def bytes_in_use(self):
         return lib.fsmmc_ctx_bytes_in_use(self.handle)
+
+    def trim(self):
+        """Give the device the buffers of freed jobs that are kept for later ones."""
+        _check(lib.fsmmc_ctx_trim(self.handle))
 
     def close(self):
         if self.handle is not None:

@@ -329,3 +329,44 @@ def test_small_jobs_hold_what_the_budget_counts(F):
         for j in held:
             j.free()
         ctx.close()
+
+
+def test_freed_direction_buffers_go_back_to_the_device(F):
+    """A freed job's direction buffer (256 MiB here) is kept for the next job, and
+    the device has it again after a trim, after the last context closed, and at
+    once under a budget.  4 MiB: the driver's own blocks."""
+    m, n, D = 1024, 64, 512
+    tgt = F.gp_target(torch.eye(D, device="cuda"), torch.ones(D, device="cuda"))
+    out = torch.zeros((m, n, D), device="cuda")
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    def once(c):
+        F.Job(c, tgt, F.ess_sampler(F.F32), m, n, 1, out=out, window=64).free()
+
+    other = F.Context(0)  # keeps whatever this process's earlier jobs left out of the figures
+    other.trim()
+    c = F.Context(0)
+    once(c)
+    c.trim()
+    start = free()
+    once(c)
+    kept = start - free()
+    once(c)
+    assert kept >= 252 << 20 and abs(start - free() - kept) <= 4 << 20
+    other.trim()  # the device's, whichever context asks
+    assert start - free() <= 4 << 20
+    other.close()
+    once(c)
+    c.close()
+    b = F.Context(0, hbm_budget_bytes=1 << 30)
+    try:
+        if free() < start - (4 << 20):  # another test's context is still open
+            b.trim()
+        assert start - free() <= 4 << 20
+        once(b)
+        assert start - free() <= 4 << 20
+    finally:
+        b.close()

@@ -36,3 +36,39 @@ def test_memory_that_kernels_reach(tmp_path):
     std::printf("%d %d ", at(hipMemoryTypeHost, 1, x + 1), at(hipMemoryTypeUnregistered, 1, x));
     """)
     assert out == ["1", "0", "1", "1", "1", "1", "0", "0"]
+
+
+def test_idle_buffers(tmp_path):
+    # kept up to the bound, the oldest given back for newer ones, handed out when
+    # they fit within a quarter; all of them back at a release and when the last
+    # context closes; none kept without one
+    out = compiled(tmp_path, """
+    static int freed;
+    IdlePool q(100, [](void* p) { freed = 10 * freed + (int)(size_t)p; });
+    auto say = [](int v) { std::printf("%d ", v); };  // a value each: arguments have no order
+    auto give = [&](int i, size_t bytes) { say(q.give((void*)(size_t)i, bytes)); };
+    auto take = [&](size_t bytes) {
+        size_t got = 0;
+        say((int)(size_t)q.take(bytes, &got));
+        say((int)got);
+    };
+    give(9, 10);
+    q.open();
+    q.open();
+    give(1, 40), give(2, 60), say(freed), give(8, 101), say(freed);
+    give(3, 30), say(freed);
+    take(45), take(61), take(50), take(30), take(30);
+    give(4, 50), give(5, 50);
+    q.release(), say(freed);
+    give(6, 100);
+    q.close(), say(freed);
+    q.close(), say(freed);
+    give(7, 1);
+    """)
+    assert " ".join(out) == ("0 "                       # no context
+                             "1 1 0 0 0 "               # up to the bound, not past it
+                             "1 1 "                     # the oldest goes
+                             "0 0 0 0 2 60 3 30 0 0 "   # more than a quarter over, too small, taken
+                             "1 1 145 "                 # released, oldest first
+                             "1 145 1456 "              # the last context
+                             "0")
