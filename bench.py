@@ -618,7 +618,7 @@ def serve_stream(n_jobs, seed):
 
 
 def nuts_step_cost(F):
-    """Microseconds per NUTS runtime step (transition, compaction, gradient)
+    """Microseconds per NUTS runtime step (transition, gradient)
     for small logistic-regression jobs of the serving mix, alone (single-job
     API) and as the only job of a server (its batch rounds of 16 steps);
     wall time over the steps issued, same draws both ways."""

@@ -194,7 +194,7 @@ __device__ __forceinline__ int drs_step(const DrsK& a, int c, DrsLane<NM>& L)
 // DX > 0: the dimension, known here: no masks, and no normals past it (of a
 // block's four, D = 1 needs one: about 330 instructions a try instead of 480).
 // With the precisions read once 1024 chains x 2000 draws at D = 1 went from 5.5
-// to 3.9 ms.
+// to 3.9 ms (D = 2 was not timed by itself, D > 2 not tried).
 template <int NM, bool SPLIT, int DX = 0>
 __global__ __launch_bounds__(256) void drs_fsm_kernel(DrsK a)
 {

@@ -169,8 +169,9 @@ __device__ __forceinline__ void put(d4 (&v)[N], int k, const d4& x)
 }
 
 // What a wave gathers along the way: the pivots of its diagonal tiles as a
-// mantissa product (at most 64 factors in [1/2, 1)) and an exponent sum, and
-// |z|^2 (the lanes of row n).  A pivot that is not positive makes its column,
+// mantissa product and an exponent sum (factors in [1/2, 1), 16 a tile: two trailing
+// tiles and, for n >= 256, one in each panel of four leading columns, so 112 at n =
+// 512 and a product of at least 2^-112), and |z|^2 (the lanes of row n).  A pivot that is not positive makes its column,
 // and with it z, NaN.
 struct GphSum {
     double pm = 1.0, zz = 0.0;

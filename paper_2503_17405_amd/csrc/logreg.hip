@@ -20,8 +20,8 @@
 //     pipeline with one barrier per chunk, so the residuals' vector work
 //     overlaps the matrix-core work of the other waves on the same SIMD
 //     (logreg_grad_tile in logreg_device.h).
-// The LDS images are unpadded with XOR-permuted 16-byte units, so operand
-// reads are free of bank conflicts.  Row slices are added in slice order (by
+// X's pieces lie in memory and in LDS in the order of the lanes that read them, r's
+// with XOR-permuted 16-byte units, so operand reads are free of bank conflicts.  Row slices are added in slice order (by
 // the NUTS transition that consumes the gradient, or by logreg_reduce_kernel
 // for the starting points); no float atomics, so every result is
 // reproducible bit for bit.  The grouped multi-job path (batch.hip) runs the

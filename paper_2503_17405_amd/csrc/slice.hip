@@ -38,7 +38,7 @@
 // density, comparison: about 300 vector instructions) and chains that wait for
 // the slowest one of their wave.  Against one chain per lane with a body per
 // state, all draws in the loop and windows of 32 draws: 1024 chains x 500 draws
-// at D = 10 25.3 -> 7.4 ms.
+// at D = 10 25.3 -> 6.9 ms.
 #include "dr_device.h"
 #include "slice_fsm.inc"
 
@@ -422,10 +422,13 @@ __global__ __launch_bounds__(256) void sl_pad_kernel(SlK a, uint32_t draw)
 }
 
 // ------------------------------------------------------------ host side
-// Chains per wave of the FSM kernel: a power of two that leaves at most 256
-// waves, one per CU -- with fewer chains a wave waits less for its slowest one
-// and skips more bodies, but waves that share a CU slow each other down.  ms a
-// job, D = 10, by chains per wave:
+// Chains per wave of the FSM kernel: the smallest power of two, up to 64, that
+// leaves at most 256 waves, one per CU -- with fewer chains a wave waits less for its
+// slowest one and skips more bodies, but waves that share a CU mostly slow each
+// other down.  The rule gives the best column of each row but the third, where it
+// takes 16 chains (5.76): one chain a wave, 16 waves a CU, is faster there and was not
+// measured at other sizes, nor is it known why 4 is slower than both.  ms a job, D =
+// 10, by chains per wave:
 //   chains x draws    64     16     4      1
 //    256 x 500       7.85   7.08   6.26   5.39
 //   1024 x 500       8.42   8.05   6.78   8.20
