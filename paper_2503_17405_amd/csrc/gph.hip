@@ -243,12 +243,13 @@ __device__ __forceinline__ double gph_dist2(const double* X, int N, int p, int i
     return s;
 }
 
-// Minus tile (I, J) of C (with y as row n).
+// Minus tile (I, J) of C (with y as row n).  KEPT: the job holds the squared distances.
+template <bool KEPT>
 __device__ __forceinline__ d4 gph_tile_of_c(const GphK& a, double tau2, double lam2, double s2, int I, int J, int lane)
 {
     const int row = 16 * I + (lane & 15), col0 = 16 * J + (lane >> 4);
     d4 v, r2;
-    if (a.r2) {
+    if constexpr (KEPT) {
         r2 = tile_load(a.r2 + (size_t)(I * (I + 1) / 2 + J) * kGphTile, lane);
     } else {
 #pragma unroll
@@ -275,7 +276,7 @@ constexpr int gph_lds_doubles() { return ((NW >= 8 ? 4 : 2) * NW + 1) * kGphTile
 // about 60 more (4 waves: 128, 3: 168, 2: 256).
 constexpr int gph_waves_per_simd(int NW) { return NW >= 8 ? 2 : (NW >= 6 ? 3 : 4); }
 
-template <int NW, bool LEAD>
+template <int NW, bool LEAD, bool KEPT>
 __device__ double gph_loglik(const GphK& a, const double* th, double* slot, double* sm)
 {
     constexpr int RW = 2 * NW;
@@ -311,7 +312,7 @@ __device__ double gph_loglik(const GphK& a, const double* th, double* slot, doub
             for (int v = 0; v < 4 * NS; ++v) {
                 const int rel = wave + NW * (v >> 2), c = v & 3;
                 if (P + rel < R && c < pc && c <= rel)
-                    tile_store(at(P + rel, P + c), lane, gph_tile_of_c(a, tau2, lam2, s2, P + rel, P + c, lane));
+                    tile_store(at(P + rel, P + c), lane, gph_tile_of_c<KEPT>(a, tau2, lam2, s2, P + rel, P + c, lane));
             }
             each<4 * NS>([&](auto v) FSMMC_INLINE {
                 const int rel = wave + NW * (v >> 2), c = v & 3;
@@ -367,7 +368,7 @@ __device__ double gph_loglik(const GphK& a, const double* th, double* slot, doub
     for (int p = 0; p <= RW; ++p) {
         const bool second = p > wave;
         const int I = base + (second ? rb : ra), J = base + (second ? RW - p : p);
-        if (I < R && J < T) put(acc, p, gph_tile_of_c(a, tau2, lam2, s2, I, J, lane));
+        if (I < R && J < T) put(acc, p, gph_tile_of_c<KEPT>(a, tau2, lam2, s2, I, J, lane));
     }
     if constexpr (LEAD) {
         // minus the leading columns' products: column k of the finished tiles
@@ -620,7 +621,7 @@ __device__ __forceinline__ int gph_next_chain(unsigned long long* q, unsigned lo
 // mode 0: FSM (to tstop or through the budget); mode 1: one draw of the
 // synchronized runtime (tstop = draw + 1), recording its largest count;
 // mode 2: vmap padding of draw `draw`.
-template <int NW, bool LEAD>
+template <int NW, bool LEAD, bool KEPT>
 __global__ __launch_bounds__(64 * NW, gph_waves_per_simd(NW)) void gph_kernel(GphK a, unsigned long long* q,
                                                                       unsigned long long base, int mode, uint32_t draw)
 {
@@ -659,7 +660,7 @@ __global__ __launch_bounds__(64 * NW, gph_waves_per_simd(NW)) void gph_kernel(Gp
             __syncthreads();
             if (!uni(S.go)) break;
             const double tp[3] = {uni(S.tp[0]), uni(S.tp[1]), uni(S.tp[2])};
-            const double lp = gph_loglik<NW, LEAD>(a, tp, slot, sm);
+            const double lp = gph_loglik<NW, LEAD, KEPT>(a, tp, slot, sm);
             if (tid == 0) {
                 ++steps;
                 if (mode == 2)
@@ -685,7 +686,7 @@ __global__ __launch_bounds__(64 * NW, gph_waves_per_simd(NW)) void gph_kernel(Gp
 
 // Starting state: theta (from x0 or a prior draw N(0, I) on the INIT stream)
 // and its log-likelihood, one block per chain.
-template <int NW, bool LEAD>
+template <int NW, bool LEAD, bool KEPT>
 __global__ __launch_bounds__(64 * NW, gph_waves_per_simd(NW)) void gph_init_kernel(GphK a, int has_x0)
 {
     __shared__ __align__(16) double sm[gph_lds_doubles<NW>()];
@@ -695,7 +696,7 @@ __global__ __launch_bounds__(64 * NW, gph_waves_per_simd(NW)) void gph_init_kern
 #pragma unroll
         for (int d = 0; d < 3; ++d)
             th[d] = has_x0 ? uni(a.th[(size_t)c * 3 + d]) : normal_at<double>(a.seed, (uint32_t)c, 0, ROLE_INIT, 0, (uint32_t)d);
-        const double lx = gph_loglik<NW, LEAD>(a, th, slot, sm);
+        const double lx = gph_loglik<NW, LEAD, KEPT>(a, th, slot, sm);
         __syncthreads();
         if (threadIdx.x == 0) {
 #pragma unroll
@@ -759,18 +760,22 @@ int gph_max_inputs() { return kGphMaxP; }
 // observations on the leading columns go through memory.
 static int gph_waves(int N) { return N < 32 ? 1 : (N < 64 ? 2 : (N < 128 ? 4 : (N < 192 ? 6 : 8))); }
 
-#define FSMMC_GPH_DISPATCH(N_, CALL)    \
-    switch (gph_waves(N_)) {           \
-    case 1: CALL(1, false); break;     \
-    case 2: CALL(2, false); break;     \
-    case 4: CALL(4, false); break;     \
-    case 6: CALL(6, false); break;     \
-    default:                           \
-        if ((N_) < 256) {              \
-            CALL(8, false);            \
-        } else {                       \
-            CALL(8, true);             \
-        }                              \
+// Jobs without the squared distances have up to 96 observations or 448 and more
+// (gph_keeps_dist).
+#define FSMMC_GPH_DISPATCH(N_, KEPT_, CALL)                              \
+    switch (gph_waves(N_)) {                                            \
+    case 1: if (KEPT_) { CALL(1, false, true); } else { CALL(1, false, false); } break; \
+    case 2: if (KEPT_) { CALL(2, false, true); } else { CALL(2, false, false); } break; \
+    case 4: if (KEPT_) { CALL(4, false, true); } else { CALL(4, false, false); } break; \
+    case 6: CALL(6, false, true); break;                                \
+    default:                                                            \
+        if ((N_) < 256) {                                               \
+            CALL(8, false, true);                                       \
+        } else if (KEPT_) {                                             \
+            CALL(8, true, true);                                        \
+        } else {                                                        \
+            CALL(8, true, false);                                       \
+        }                                                               \
     }
 
 // Blocks of the persistent kernel: what the chip holds at once, at most one per chain.
@@ -781,9 +786,9 @@ static hipError_t gph_blocks(const JobDev& j, int* blocks)
         hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
         cus = v;
     hipError_t e = hipSuccess;
-#define FSMMC_GPH_OCC(NW, LEAD) \
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)gph_kernel<NW, LEAD>, 64 * NW, 0)
-    FSMMC_GPH_DISPATCH(j.N, FSMMC_GPH_OCC)
+#define FSMMC_GPH_OCC(NW, LEAD, KEPT) \
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)gph_kernel<NW, LEAD, KEPT>, 64 * NW, 0)
+    FSMMC_GPH_DISPATCH(j.N, true, FSMMC_GPH_OCC)
 #undef FSMMC_GPH_OCC
     *blocks = std::max(1, std::min(j.m, cus * std::max(1, per_cu)));
     return e;
@@ -799,8 +804,8 @@ size_t gph_dist_bytes(int N)
 
 // Whether a job keeps the squared distances.  Under an HBM budget only where it then
 // holds no more than the vector Cholesky before this one did (a work matrix of n
-// rounded up to 32 per block above n = 96, nothing up to there), so that what
-// fitted a budget still does; the kernels form the distances themselves otherwise
+// rounded up to 32 per block above n = 96, nothing up to there; between 97 and 447 that
+// is always enough), so that what fitted a budget still does; the kernels form the distances themselves otherwise
 // (6 inputs: n = 25, 1024 chains x 100 draws 4.0 -> 6.1 ms, n = 63, 512 x 60 8.5 ->
 // 12.2, n = 96, 1024 x 40 13.9 -> 18.7).
 bool gph_keeps_dist(const JobDev& j, bool budget)
@@ -832,19 +837,19 @@ hipError_t gph_init_state(const JobDev& j, const void* x0, hipStream_t s)
         hipError_t e = hipMemcpyAsync(j.x, x0, (size_t)j.m * 3 * 8, hipMemcpyDeviceToDevice, s);
         if (e != hipSuccess) return e;
     }
-#define FSMMC_GPH_INIT(NW, LEAD) \
-    hipLaunchKernelGGL((gph_init_kernel<NW, LEAD>), dim3(j.pblocks), dim3(64 * NW), 0, s, gph_view(j), x0 ? 1 : 0)
-    FSMMC_GPH_DISPATCH(j.N, FSMMC_GPH_INIT)
+#define FSMMC_GPH_INIT(NW, LEAD, KEPT) \
+    hipLaunchKernelGGL((gph_init_kernel<NW, LEAD, KEPT>), dim3(j.pblocks), dim3(64 * NW), 0, s, gph_view(j), x0 ? 1 : 0)
+    FSMMC_GPH_DISPATCH(j.N, j.L != nullptr, FSMMC_GPH_INIT)
 #undef FSMMC_GPH_INIT
     return hipGetLastError();
 }
 
 hipError_t gph_run(const JobDev& j, int mode, uint32_t draw, unsigned long long* ticket, hipStream_t s)
 {
-#define FSMMC_GPH_RUN(NW, LEAD)                                                                             \
-    hipLaunchKernelGGL((gph_kernel<NW, LEAD>), dim3(j.pblocks), dim3(64 * NW), 0, s, gph_view(j),           \
+#define FSMMC_GPH_RUN(NW, LEAD, KEPT)                                                                       \
+    hipLaunchKernelGGL((gph_kernel<NW, LEAD, KEPT>), dim3(j.pblocks), dim3(64 * NW), 0, s, gph_view(j),     \
                        (unsigned long long*)j.queue, *ticket, mode, draw)
-    FSMMC_GPH_DISPATCH(j.N, FSMMC_GPH_RUN)
+    FSMMC_GPH_DISPATCH(j.N, j.L != nullptr, FSMMC_GPH_RUN)
 #undef FSMMC_GPH_RUN
     *ticket += (unsigned long long)j.m + (unsigned long long)j.pblocks;
     return hipGetLastError();
