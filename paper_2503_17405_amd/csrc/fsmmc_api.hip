@@ -179,11 +179,16 @@ static hipError_t device_sync(int device)
 
 // Device memory of a job: job_want charges the budget for an array and notes where
 // its pointer goes, job_place allocates what was noted since the last call.  Arrays
-// of up to kSmallArray share one allocation of just their size (each rounded up to
-// 256 bytes) and one clear: a job has about twenty, and an allocation, a clear and a
-// free of each were a third of a millisecond.  zero: cleared, else a job's one
+// of up to small_array() (32 bytes a chain, 64 KiB to 2 MiB) share one allocation of
+// just their size (each rounded up to 256 bytes) and one clear: a job has about
+// twenty, and an allocation, a clear and a free of each were a third of a
+// millisecond; larger ones gain nothing (1024 slice chains, 2 MB of counts: 61 us to
+// create a job with them apart, 72 with them in).  zero: cleared, else a job's one
 // direction buffer.
-constexpr size_t kSmallArray = 2u << 20;
+static size_t small_array(const fsmmc_job* j)
+{
+    return std::min<size_t>(2u << 20, std::max<size_t>(64u << 10, (size_t)j->d.m * 32));
+}
 
 static fsmmc_status job_want(fsmmc_job* j, void* where, size_t bytes, bool zero = true)
 {
@@ -214,8 +219,8 @@ static fsmmc_status job_place(fsmmc_job* j)
     const auto no_memory = [](hipError_t e) {
         return fail(FSMMC_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
     };
-    size_t small = 0;
-    for (const fsmmc_job::Want& w : j->wants) small += w.zero && w.bytes <= kSmallArray ? cut(w.bytes) : 0;
+    size_t small = 0, most = small_array(j);
+    for (const fsmmc_job::Want& w : j->wants) small += w.zero && w.bytes <= most ? cut(w.bytes) : 0;
     unsigned char* next = nullptr;
     if (small) {
         void* p = nullptr;
@@ -232,7 +237,7 @@ static fsmmc_status job_place(fsmmc_job* j)
             hipError_t e = p ? hipSuccess : device_malloc(&p, w.bytes);
             if (e != hipSuccess) return no_memory(e);
             j->dirs = p;
-        } else if (w.bytes <= kSmallArray) {
+        } else if (w.bytes <= most) {
             p = next;
             next += cut(w.bytes);
         } else {
