@@ -195,7 +195,7 @@ size_t fsmmc_ctx_bytes_in_use(const fsmmc_ctx* ctx);
 /* ESS direction buffers of freed jobs stay allocated for the next jobs, up to
  * 1 GiB a device (the oldest are freed for newer ones) and only those of contexts
  * without a budget; fsmmc_ctx_bytes_in_use does not count them.  They go back to
- * the device when its last context is destroyed, when an allocation of this
+ * the device when the last such context is destroyed, when an allocation of this
  * library on the device fails (it is then tried again), and at this call, for
  * callers that need the memory elsewhere.  Errors: EINVAL. */
 fsmmc_status fsmmc_ctx_trim(fsmmc_ctx* ctx);

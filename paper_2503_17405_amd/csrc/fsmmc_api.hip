@@ -369,7 +369,7 @@ fsmmc_status fsmmc_ctx_create(int device, size_t hbm_budget_bytes, fsmmc_ctx** o
     c->device = device;
     c->budget = hbm_budget_bytes;
     c->idle = idle_pool(device);
-    c->idle->open();
+    if (!c->budget) c->idle->open();
     *out = c;
     return FSMMC_OK;
 }
@@ -378,7 +378,7 @@ fsmmc_status fsmmc_ctx_destroy(fsmmc_ctx* ctx)
 {
     if (!ctx) return fail(FSMMC_EINVAL, "ctx is NULL");
     if (ctx->jobs.load() != 0) return fail(FSMMC_EBUSY, "context still has jobs");
-    ctx->idle->close();
+    if (!ctx->budget) ctx->idle->close();
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     delete ctx;
     return FSMMC_OK;

@@ -7,9 +7,9 @@
 
 namespace fsmmc {
 
-// One per device, shared by its contexts, at most `cap` bytes: a buffer that does not
-// fit beside the others takes the place of the oldest.  The last context to close
-// gives everything back.  Nothing on the device may use a buffer given to the pool.
+// One per device, shared by its contexts without an HBM budget, at most `cap` bytes: a
+// buffer that does not fit beside the others takes the place of the oldest.  The last
+// of those contexts to close gives everything back.  Nothing on the device may use a buffer given to the pool.
 class IdlePool {
 public:
     IdlePool(size_t cap, void (*free)(void*)) : cap_(cap), free_(free) {}
